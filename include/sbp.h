@@ -191,8 +191,9 @@ int sbp_record(sbp_handle h, int nrec, const int* ijk, void* out_device, int max
  * (volume terms, penalties, sources) and is fused with the stage update
  * dQ <- A_k dQ + dt RHS, Q <- Q + B_k dQ.  Asynchronous on the stream.
  * SBP_ESTATE before sbp_set_material.
- * The call's first step is issued as direct launches (five stages of
- * stage, edge, penalty and source kernels, the receivers, a clock tick);
+ * The call's first step is issued as direct launches (five stages of the
+ * tile kernel, or of stage, edge, penalty and source kernels, the receivers,
+ * a clock tick);
  * every later step is one replay of a HIP graph holding the same launches,
  * captured on first use and again whenever dt, the sources, the receivers or
  * the launch shape change -- when none of the step's kernels uses scratch
@@ -347,7 +348,10 @@ int sbp_energy(sbp_handle h, double* E);
 /*
  * Launch shape of the stage kernel: ty rows of 64 points per thread block
  * (8 or 16; 16 only for SBP_F32 at orders 2 to 7, else SBP_EINVAL) and
- * zchunk planes per block along s (>= 1; 0 = automatic).
+ * zchunk planes per block along s (>= 1; 0 = automatic).  Without this call
+ * a handle of up to 1.75 million nodes runs a stage as one launch of the
+ * tile kernel, which has no launch shape; with it the stage kernel runs, with
+ * the shape given.
  * Does not change results beyond floating-point summation order (it does
  * not change it at all: every node is computed by the same instructions).
  */
@@ -371,6 +375,8 @@ int sbp_set_addressing(sbp_handle h, int plain);
  * q column and last r row, and the boundary penalties: one launch in
  * SBP_F32) with HIP events on the handle's stream; the host
  * waits for each stage to finish, so stepping is slower while it is on.
+ * With the tile kernel (see sbp_set_launch) the same two sets of nodes are
+ * computed, and timed, by two launches of it.
  * sbp_set_profiling(h, 0) switches it off.  sbp_profile returns the average
  * durations in milliseconds (*stage_ms, *edge_ms), the number of timed stages
  * and the number of nodes one stage-kernel launch computes; any output
@@ -384,9 +390,11 @@ int sbp_profile(sbp_handle h, double* stage_ms, double* edge_ms, long long* nsta
  * Launch-shape autotuner.  Times `reps` right-hand-side evaluations of the
  * handle's own grid for each candidate launch shape (tile height 8, and 16
  * for SBP_F32 at orders up to 7; the cost model's number of s-chunks and one
- * fewer / one more) and keeps the fastest, as sbp_set_launch would.  Writes
- * the chosen tile height, s-chunk length and its time per evaluation (ms) to
- * the outputs (each may be NULL).  The state and time are not changed; call
+ * fewer / one more) and keeps the fastest, as sbp_set_launch would -- or the
+ * tile kernel, where that is the automatic choice (see sbp_set_launch) and
+ * faster than every shape.  Writes the tile height and s-chunk length of the
+ * fastest shape and the time per evaluation (ms) of what it keeps to the
+ * outputs (each may be NULL).  The state and time are not changed; call
  * it between steps.  Synchronises the stream.
  */
 int sbp_autotune(sbp_handle h, int reps, int* ty, int* zchunk, double* ms);

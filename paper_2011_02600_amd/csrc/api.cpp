@@ -17,6 +17,7 @@
 #include "adjoint.hpp"
 #include "host_math.hpp"
 #include "kernels.hpp"
+#include "tile.hpp"
 
 using namespace sbp;
 
@@ -90,7 +91,7 @@ struct sbp_ctx {
   std::size_t ws_bytes = 0;
   // byte offsets in the workspace
   std::size_t off_qa = 0, off_qb = 0, off_dq = 0, off_coef = 0, off_face[6] = {}, off_src = 0,
-              off_rec = 0, off_part = 0, off_bounds = 0, off_tab = 0, off_scl = 0, off_eqc = 0, off_batch = 0,
+              off_rec = 0, off_part = 0, off_bounds = 0, off_tab = 0, off_tw = 0, off_scl = 0, off_eqc = 0, off_batch = 0,
               total = 0;
   std::size_t face_n[6] = {};
   int px = 0;
@@ -113,6 +114,8 @@ struct sbp_ctx {
   int nxt = 0, nyt = 0, nzc = 0;
   int ex = 0, ey = 0;   // last q column / last r row computed by the edge kernel
   bool bounds_dirty = true;
+  bool shape_set = false;  // launch shape ty, zchunk of the caller's (sbp_set_launch, sbp_autotune)
+  TileShape tile{};        // tile kernel's launch shape
   // launch timing (sbp_set_profiling)
   bool prof = false;
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
@@ -257,6 +260,7 @@ void layout(sbp_ctx* h) {
   h->off_part = take(kMaxPart * sizeof(double));
   h->off_bounds = take((std::size_t)(g.nq + g.nr + g.ns + 16) * sizeof(int));
   h->off_tab = take((std::size_t)kClosureTab * kMaxM * kMaxCols * es);
+  h->off_tw = take((std::size_t)2 * (2 * kMaxM + 1) * (kMaxM + kMaxCols) * es);
   h->off_scl = take((std::size_t)2 * kMaxM * 6 * h->plane * es);
   // single precision: the stage kernel's copies of the last column's q
   // closure inputs (StageArgs::eqc), sized for the widest closure row
@@ -481,9 +485,25 @@ int prepare_bounds(sbp_ctx* h) {
   HIPCHK(hipMemcpyAsync(h->ws + h->off_bounds, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice,
                         h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
+  h->tile = tile_shape(g.nq, g.nr, g.ns, h->cl.m);
   h->bounds_dirty = false;
   ++h->gen;
   return SBP_OK;
+}
+
+// Whether the grid's stages run as one tile-kernel launch each, else as the
+// stage kernel's march along s with the edge and penalty launches (always with
+// a launch shape of the caller's or plain addressing).  The tile kernel reads
+// the planes around a node again for every node, which costs little while the
+// caches hold them; the march reads them once, in a chain of planes whose
+// latency small grids cannot hide.  They meet between 1.6 and 2.1 million
+// nodes in both precisions (us per stage, tile and march: order 6 single
+// 1.44e6 nodes 96 and 120, 2.15e6 141 and 136; double 1.44e6 214 and 231,
+// 2.15e6 311 and 298; order 3 double 1.61e6 189 and 214).
+constexpr std::size_t kTileNodes = 1750000;
+
+bool use_tile(const sbp_ctx* h) {
+  return !h->shape_set && !h->plain && h->g.n <= kTileNodes;
 }
 
 double stf_value(const Src& s, double t) {
@@ -532,6 +552,9 @@ StageArgs<T> stage_args(sbp_ctx* h) {
   a.scl = (T*)(h->ws + h->off_scl);
   a.eqc = sizeof(T) == 4 ? (T*)(h->ws + h->off_eqc) : nullptr;
   a.nsrc = 0;
+  a.src_stride = kMaxSources;
+  a.tw = (const T*)(h->ws + h->off_tw);
+  a.tile = h->tile;
   return a;
 }
 
@@ -566,7 +589,7 @@ template <typename T>
 bool fuse_sources(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, bool rhs_only,
                   const StepClock* clock) {
   a.nsrc = 0;
-  if (sizeof(T) != 4 || h->src.empty()) return false;
+  if ((sizeof(T) != 4 && !use_tile(h)) || h->src.empty()) return false;
   const SourceArgs<T> s = source_args<T>(h, k, dt, tstage, rhs_only, nullptr);
   a.nsrc = (int)h->src.size();
   a.src_w = s.width;
@@ -625,9 +648,22 @@ int run_stage(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, bool
   const bool fused = fuse_sources<T>(h, a, k, dt, tstage, rhs_only, clock);
   const bool prof = h->prof && st == h->stream;
   if (prof) HIPCHK(hipEventRecord(h->ev[0], st));
-  HIPCHK(launch_stage<T>(h->order, h->ty, a, st));
-  if (prof) HIPCHK(hipEventRecord(h->ev[1], st));
-  HIPCHK(edge_and_penalties<T>(h, a, st));
+  if (use_tile(h)) {
+    // timed, the launch is split: the nodes sbp_profile reports, then the
+    // last q column and r row
+    if (prof) a.tile.part = 1;
+    HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, a, st));
+    if (prof) {
+      HIPCHK(hipEventRecord(h->ev[1], st));
+      a.tile.part = 2;
+      HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, a, st));
+      a.tile.part = 0;
+    }
+  } else {
+    HIPCHK(launch_stage<T>(h->order, h->ty, a, st));
+    if (prof) HIPCHK(hipEventRecord(h->ev[1], st));
+    HIPCHK(edge_and_penalties<T>(h, a, st));
+  }
   if (prof) {
     HIPCHK(hipEventRecord(h->ev[2], st));
     HIPCHK(hipEventSynchronize(h->ev[2]));
@@ -714,7 +750,8 @@ int do_steps(sbp_ctx* h, int nsteps, double dt) {
   // graph-launched double-precision kernel with a large private segment
   // once ended in a memory fault whose cause was not found; kernels that
   // spill launch eagerly)
-  const bool use_graph = h->graphs && !h->prof && step_scratch<T>(h->order, h->ty) == 0;
+  const bool use_graph = h->graphs && !h->prof &&
+                         (use_tile(h) ? tile_scratch<T>(h->order) : step_scratch<T>(h->order, h->ty)) == 0;
   for (int n0 = 0; n0 < nsteps; n0 += kTabSteps) {
     const int nc = std::min(kTabSteps, nsteps - n0);
     const int part = h->tab_next;
@@ -1336,7 +1373,8 @@ namespace {
 
 // Launch-shape autotuner: times `reps` right-hand-side evaluations (stage and
 // edge kernel, sources off) for each candidate tile height and number of
-// s-chunks and keeps the fastest.  A right-hand-side evaluation writes only
+// s-chunks, and the tile kernel where it is the automatic choice, and keeps
+// the fastest.  A right-hand-side evaluation writes only
 // the Runge-Kutta register and the second state buffer, which hold nothing
 // between steps, so the state is untouched.
 template <typename T>
@@ -1344,6 +1382,7 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
   std::vector<int> tys{8};
   if (sizeof(T) == 4 && h->order <= 7) tys.push_back(16);  // 16-row order-8 tiles exceed the LDS
   const std::vector<Src> saved = h->src;
+  const bool was_set = h->shape_set;
   h->src.clear();
   hipEvent_t e0 = nullptr, e1 = nullptr;
   HIPCHK(hipEventCreate(&e0));
@@ -1351,7 +1390,33 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
   double best = -1.0;
   int bty = h->ty, bzc = h->zchunk;
   int rc = SBP_OK;
+  // ms per evaluation with the handle's settings
+  auto time_rhs = [&](double* per) -> int {
+    int rc = prepare_bounds(h);
+    if (rc) return rc;
+    StageArgs<T> a = stage_args<T>(h);
+    T* qa = (T*)(h->ws + h->off_qa);
+    T* qb = (T*)(h->ws + h->off_qb);
+    T* qin = h->cur ? qb : qa;
+    T* qout = h->cur ? qa : qb;
+    if ((rc = run_stage<T>(h, a, 0, 1.0, h->t, true, qin, qout, h->stream, nullptr))) return rc;  // warm-up
+    if (hipEventRecord(e0, h->stream) != hipSuccess) return fail(SBP_EHIP, "hipEventRecord failed");
+    for (int r = 0; r < reps; ++r)
+      if ((rc = run_stage<T>(h, a, 0, 1.0, h->t, true, qin, qout, h->stream, nullptr))) return rc;
+    float ms = 0.f;
+    if (hipEventRecord(e1, h->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+        hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+      return fail(SBP_EHIP, "event timing failed");
+    *per = ms / reps;
+    return SBP_OK;
+  };
+  // the automatic choice, where that is the tile kernel
+  double tile_ms = -1.0;
+  h->shape_set = false;
+  if (use_tile(h)) rc = time_rhs(&tile_ms);
+  h->shape_set = true;
   for (int ty : tys) {
+    if (rc) break;
     if (ty < h->cl.m) continue;
     // the cost model's chunk count, and one fewer / more chunks
     h->ty = ty;
@@ -1363,24 +1428,8 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
       h->ty = ty;
       h->zchunk = (h->g.ns + nz - 1) / nz;
       h->bounds_dirty = true;
-      if ((rc = prepare_bounds(h))) break;
-      StageArgs<T> a = stage_args<T>(h);
-      T* qa = (T*)(h->ws + h->off_qa);
-      T* qb = (T*)(h->ws + h->off_qb);
-      T* qin = h->cur ? qb : qa;
-      T* qout = h->cur ? qa : qb;
-      if ((rc = run_stage<T>(h, a, 0, 1.0, h->t, true, qin, qout, h->stream, nullptr))) break;  // warm-up
-      if (hipEventRecord(e0, h->stream) != hipSuccess) { rc = fail(SBP_EHIP, "hipEventRecord failed"); break; }
-      for (int r = 0; r < reps && rc == SBP_OK; ++r)
-        rc = run_stage<T>(h, a, 0, 1.0, h->t, true, qin, qout, h->stream, nullptr);
-      if (rc) break;
-      float ms = 0.f;
-      if (hipEventRecord(e1, h->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-          hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
-        rc = fail(SBP_EHIP, "event timing failed");
-        break;
-      }
-      const double per = ms / reps;
+      double per = 0.0;
+      if ((rc = time_rhs(&per))) break;
       if (best < 0 || per < best) {
         best = per;
         bty = ty;
@@ -1395,7 +1444,14 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
   h->ty = bty;
   h->zchunk = bzc;
   h->bounds_dirty = true;
-  if (rc) return rc;
+  if (rc) {
+    h->shape_set = was_set;
+    return rc;
+  }
+  if (tile_ms >= 0 && (best < 0 || tile_ms <= best)) {
+    h->shape_set = false;
+    best = tile_ms;
+  }
   if (best_ty) *best_ty = bty;
   if (best_zchunk) *best_zchunk = bzc;
   if (best_ms) *best_ms = best;
@@ -1457,8 +1513,12 @@ int stage_explicit(sbp_ctx* h, const StageArgs<T>& base, int k, double dt, doubl
   b.sat = sat ? 1 : 0;
   const bool fused = sources && fuse_sources<T>(h, b, k, dt, tstage, rhs_only, nullptr);
   if (!sources) b.nsrc = 0;
-  HIPCHK(launch_stage<T>(h->order, h->ty, b, h->stream));
-  HIPCHK(edge_and_penalties<T>(h, b, h->stream));
+  if (use_tile(h)) {
+    HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, b, h->stream));
+  } else {
+    HIPCHK(launch_stage<T>(h->order, h->ty, b, h->stream));
+    HIPCHK(edge_and_penalties<T>(h, b, h->stream));
+  }
   if (sources && !fused && !h->src.empty()) {
     SourceArgs<T> s = source_args<T>(h, k, dt, tstage, rhs_only, qout);
     s.dq = dq;
@@ -1737,6 +1797,21 @@ int sbp_init_grid(sbp_handle* out, int nq, int nr, int ns, const double* xyz, in
         tab[3 * kMaxM * kMaxCols + o] = -h->cl.dp[r][c];
       }
     rc = upload_vec(h, h->off_tab, tab);
+    // the tile kernel's weight rows: the same closure rows, and the interior
+    // stencils, over ascending columns
+    const int m = h->cl.m, nc = h->cl.ncol, wl = m + nc, wr = 2 * m + 1;
+    std::vector<double> tw((std::size_t)2 * wr * wl, 0.0);
+    for (int pm = 0; pm < 2; ++pm) {
+      double* t = tw.data() + (std::size_t)pm * wr * wl + m;
+      for (int s = 0; s <= h->cl.r + h->cl.q; ++s)
+        t[s] = pm == 0 ? h->cl.alpha[s] : -h->cl.alpha[h->cl.r + h->cl.q - s];
+      for (int r = 0; r < m; ++r)
+        for (int c = 0; c < nc; ++c) {
+          t[(1 + r) * wl + c] = pm == 0 ? h->cl.dp[r][c] : h->cl.dm[r][c];
+          t[(1 + m + r) * wl + nc - 1 - c] = pm == 0 ? -h->cl.dm[r][c] : -h->cl.dp[r][c];
+        }
+    }
+    if (!rc) rc = upload_vec(h, h->off_tw, tw);
     if (rc) {
       std::string keep = g_err;
       delete h;
@@ -2086,6 +2161,7 @@ int sbp_set_launch(sbp_handle h, int ty, int zchunk) {
   if (zchunk < 0) return fail(SBP_EINVAL, "zchunk must be >= 0");
   h->ty = ty;
   h->zchunk = zchunk;
+  h->shape_set = true;
   h->bounds_dirty = true;
   ++h->gen;
   return SBP_OK;

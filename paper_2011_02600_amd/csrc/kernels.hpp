@@ -11,6 +11,27 @@ namespace sbp {
 
 struct StepClock;
 
+// Split of n points into T tiles: the first e0 points, then tiles of p
+// points, those after tile thr of p + 1; with last > 0 the last tile holds
+// `last` points.
+struct TileAxis {
+  int n, T, e0, p, thr, last;
+  __host__ __device__ int start(int t) const {
+    if (t <= 0) return 0;
+    if (t >= T) return n;
+    if (t == T - 1 && last > 0) return n - last;
+    const int u = t - 1;
+    return e0 + u * p + (u > thr ? u - thr : 0);
+  }
+};
+
+// launch shape of the tile kernel: tiles along q and r, one plane each
+struct TileShape {
+  TileAxis q, r;
+  int ntiles;
+  int part;  // nodes computed: 0 all, 1 i < nq-1 and j < nr-ey, 2 the others
+};
+
 template <typename T>
 struct StageArgs {
   const T* qin;       // 9 fields, current stage input
@@ -59,6 +80,13 @@ struct StageArgs {
   // h D- at the left end, then -h D- and -h D+ (the right-end rows of h D+
   // and h D- read against reversed columns)
   const T* tab;
+  // rows of the source-time table (entries per (step, stage)) and this grid's
+  // first entry in one
+  int src_stride, src_off;
+  // tile kernel: weight rows [D+, D-][interior, left closure, right closure]
+  // over ascending columns, each after m zeros; launch shape
+  const T* tw;
+  TileShape tile;
 };
 
 constexpr int kClosureTab = 4;

@@ -1,0 +1,74 @@
+"""The tile stage kernel (one launch per stage, grids of up to 1.75 million
+nodes) against the stage kernel's march, which a caller's launch shape selects:
+right-hand side and Runge-Kutta steps agree to rounding at the sizes where
+tiles end -- 32 k, 32 k + 1 (a last tile of 33 columns), a remainder smaller
+than a closure, 8 k and 7 k rows, the smallest grids -- for every order."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # order, (ns, nr, nq)
+    (2, (4, 4, 4)), (2, (9, 17, 64)), (2, (5, 9, 33)),
+    (3, (6, 6, 6)), (3, (7, 16, 34)), (3, (13, 15, 65)),
+    (4, (8, 8, 8)), (4, (17, 64, 32)), (4, (9, 29, 35)), (4, (11, 22, 129)),
+    (5, (10, 10, 10)), (5, (12, 16, 36)), (5, (21, 14, 97)),
+    (6, (12, 12, 12)), (6, (13, 17, 33)), (6, (15, 15, 37)), (6, (12, 65, 65)), (6, (30, 31, 70)),
+    (7, (14, 14, 14)), (7, (15, 17, 38)), (7, (14, 21, 65)),
+    (8, (16, 16, 16)), (8, (17, 17, 39)), (8, (16, 23, 65)),
+]
+
+
+def rel_max(x, y):
+    """largest difference per field over the field's largest value"""
+    ax = tuple(range(1, x.ndim))
+    return float((np.abs(x - y).max(axis=ax) / np.maximum(np.abs(y).max(axis=ax), 1e-300)).max())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("order,shape", SHAPES)
+def test_tile_kernel_equals_the_march(order, shape, dtype):
+    from paper_2011_02600_amd import sbp
+    print("case: tile kernel order %d shape %s %s" % (order, shape, dtype), flush=True)
+    ns, nr, nq = shape
+    xyz = W.warped_mesh(nq, nr, ns, seed=order + nq, amp=0.02)
+    med = W.random_medium(shape, 3)
+    Q = W.random_state(shape, 5, smooth=(dtype == "f32"))
+    out = {}
+    for path in ("tile", "march"):
+        s = sbp.Solver(xyz, order=order, dtype=dtype, gamma=[1.0, 0.0, -1.0, 0.4, 0.0, 1.0], sat_variant=order % 2)
+        s.set_material(*med)
+        s.add_source((0.1, 0.52, 0.61), (0.3, -0.1, 0.2, 1.0, -0.5, 0.25), 0, 2.0, 0.1)
+        s.add_source((0.97, 0.98, 0.03), (0.0, 0.5, 0.2, 0.0, 1.0, 0.0), 1, 0.1, 0.0)
+        if path == "march":
+            s.set_launch(8, 0)
+        s.set_state(Q, 0.05)
+        r = s.rhs(0.13).cpu().numpy().astype(np.float64)
+        traces = s.record([(0, 0, 0), (nq - 1, nr - 1, ns - 1), (nq // 2, nr // 2, ns // 2)], 3)
+        s.fill_scratch(float("nan"))
+        s.step(3, 1e-4)
+        out[path] = (r, s.get_state().cpu().numpy().astype(np.float64),
+                     traces.cpu().numpy().astype(np.float64).transpose(2, 0, 1))
+        s.close()
+    tol = 1e-5 if dtype == "f32" else 1e-12
+    errs = [rel_max(a, b) for a, b in zip(out["tile"], out["march"])]
+    print("  rel max: rhs %.1e, state %.1e, traces %.1e" % tuple(errs), flush=True)
+    assert all(e <= tol for e in errs)
+
+
+def test_autotune_considers_the_tile_kernel():
+    """A small grid keeps the tile kernel, and a caller's shape replaces it."""
+    from paper_2011_02600_amd import sbp
+    print("case: autotune with the tile kernel", flush=True)
+    s = sbp.Solver(W.unit_cube(65, 41, 29), order=4, dtype="f32")
+    s.set_material(2.7, 6.0, 3.464)
+    s.set_state(W.random_state((29, 41, 65), 1, smooth=True))
+    _, _, ms = s.autotune(5)
+    a = s.rhs().clone()
+    s.set_launch(8, 0)
+    b = s.rhs()
+    assert ms > 0 and torch.allclose(a, b, rtol=1e-4, atol=1e-4 * float(b.abs().max()))
+    s.close()
