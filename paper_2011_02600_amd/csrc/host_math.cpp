@@ -7,44 +7,73 @@
 
 namespace sbp {
 
+namespace {
+
+// acc[a] += w f[a], or -= for neg, for a = 0 .. n-1
+inline void add_row(double* acc, double w, const double* f, int n, bool neg) {
+  if (neg)
+    for (int a = 0; a < n; ++a) acc[a] -= w * f[a];
+  else
+    for (int a = 0; a < n; ++a) acc[a] += w * f[a];
+}
+
+}  // namespace
+
+// The sums run tap by tap over rows of consecutive values (along q the
+// interior nodes of a line, along r and s the lines' nodes side by side), so
+// that they read memory in order and vectorise; each value's own sum is taken
+// in the order of the taps.
 void apply_axis(const Closure& c, const Grid3& g, const double* in, double* out, int ax, int kind) {
   const int N = g.len(ax);
   const std::size_t stride = ax == 0 ? 1 : (ax == 1 ? (std::size_t)g.nq : (std::size_t)g.nq * g.nr);
   const double ih = N - 1;
   const int R = c.r, m = c.m, nt = c.r + c.q + 1;
-  // every line along ax
-  const int n1 = ax == 0 ? g.nr : g.nq;
+  const bool plus = kind != 1, minus = kind != 0;
+  std::vector<double> vp(g.nq, 0.0), vm(g.nq, 0.0);
+  auto store = [&](double* o, int n) {
+    for (int a = 0; a < n; ++a) o[a] = ih * (kind == 0 ? vp[a] : (kind == 1 ? vm[a] : 0.5 * (vp[a] + vm[a])));
+  };
+  // n consecutive lines at line position i: f, o at position 0 of the first
+  auto closure_rows = [&](const double* f, double* o, int i, int n) {
+    std::fill(vp.begin(), vp.begin() + n, 0.0);
+    std::fill(vm.begin(), vm.begin() + n, 0.0);
+    for (int cc = 0; cc < c.ncol; ++cc) {
+      if (i < m) {
+        if (plus) add_row(vp.data(), c.dp[i][cc], f + (std::size_t)cc * stride, n, false);
+        if (minus) add_row(vm.data(), c.dm[i][cc], f + (std::size_t)cc * stride, n, false);
+      } else {  // right end: D+ = -flip(D-), D- = -flip(D+)
+        const int row = N - 1 - i;
+        if (plus) add_row(vp.data(), c.dm[row][cc], f + (std::size_t)(N - 1 - cc) * stride, n, true);
+        if (minus) add_row(vm.data(), c.dp[row][cc], f + (std::size_t)(N - 1 - cc) * stride, n, true);
+      }
+    }
+    store(o + (std::size_t)i * stride, n);
+  };
+  // n consecutive values whose first lies at interior position i
+  auto interior_rows = [&](const double* f, double* o, int i, int n) {
+    std::fill(vp.begin(), vp.begin() + n, 0.0);
+    std::fill(vm.begin(), vm.begin() + n, 0.0);
+    for (int s = 0; s < nt; ++s) {
+      if (plus) add_row(vp.data(), c.alpha[s], f + (std::size_t)(i - R + s) * stride, n, false);
+      if (minus) add_row(vm.data(), c.alpha[s], f + (std::size_t)(i + R - s) * stride, n, true);
+    }
+    store(o + (std::size_t)i * stride, n);
+  };
+  const int n1 = ax == 0 ? g.nr : 1;  // ax > 0: the g.nq lines side by side at once
   const int n2 = ax == 2 ? g.nr : g.ns;
   for (int b = 0; b < n2; ++b) {
     for (int a = 0; a < n1; ++a) {
-      std::size_t base;
-      if (ax == 0) base = g.idx(0, a, b);
-      else if (ax == 1) base = g.idx(a, 0, b);
-      else base = g.idx(a, b, 0);
+      const std::size_t base = ax == 0 ? g.idx(0, a, b) : (ax == 1 ? g.idx(0, 0, b) : g.idx(0, b, 0));
       const double* f = in + base;
       double* o = out + base;
-      for (int i = 0; i < N; ++i) {
-        double vp = 0, vm = 0;
-        if (i >= m && i < N - m) {
-          for (int s = 0; s < nt; ++s) {
-            vp += c.alpha[s] * f[(std::size_t)(i - R + s) * stride];
-            vm -= c.alpha[s] * f[(std::size_t)(i + R - s) * stride];
-          }
-        } else if (i < m) {
-          for (int cc = 0; cc < c.ncol; ++cc) {
-            vp += c.dp[i][cc] * f[(std::size_t)cc * stride];
-            vm += c.dm[i][cc] * f[(std::size_t)cc * stride];
-          }
-        } else {
-          // right end: D+ = -flip(D-), D- = -flip(D+)
-          const int row = N - 1 - i;
-          for (int cc = 0; cc < c.ncol; ++cc) {
-            vp -= c.dm[row][cc] * f[(std::size_t)(N - 1 - cc) * stride];
-            vm -= c.dp[row][cc] * f[(std::size_t)(N - 1 - cc) * stride];
-          }
-        }
-        o[(std::size_t)i * stride] = ih * (kind == 0 ? vp : (kind == 1 ? vm : 0.5 * (vp + vm)));
+      const int n = ax == 0 ? 1 : g.nq;
+      for (int i = 0; i < m; ++i) closure_rows(f, o, i, n);
+      if (ax == 0) {
+        interior_rows(f, o, m, N - 2 * m);
+      } else {
+        for (int i = m; i < N - m; ++i) interior_rows(f, o, i, n);
       }
+      for (int i = N - m; i < N; ++i) closure_rows(f, o, i, n);
     }
   }
 }
