@@ -217,35 +217,41 @@ int sbp_set_graphs(sbp_handle h, int on);
  * Advance n handles (1 <= n <= 64) by nsteps steps each, handle i with step
  * dt[i] (host array of n doubles): batched stepping of many independent
  * sources or media ("shots") on grids of uneven size and mixed interior
- * orders.  Per Runge-Kutta stage one launch covers a list of the
- * stage-kernel tiles and edge-kernel blocks of every handle, split into one
- * segment per XCD of equal estimated cost, longest items first (block b of
- * the launch runs item b / 8 of segment b % 8); then one launch injects
- * every point source; per step one launch records every receiver.  Where
- * the kernels use no scratch memory (SBP_F32) each step is a replay of a
- * graph captured for the call (even and odd steps); otherwise the same
- * launches are issued directly.  The
- * source-time factors come from a device table uploaded every 64 steps.
- * Every grid uses
- * 8-row tiles and one s-chunk length for the batch (from
+ * orders.
+ * Handles of up to 1.75 million nodes (without plain addressing) run in
+ * groups small enough for a group's fields to stay in the memory-side cache,
+ * one group's steps after the other's; per stage and interior order of a
+ * group one launch of the tile kernel covers all its grids, penalties and
+ * sources included.  The larger handles run together: per stage one launch
+ * covers a list of the stage-kernel tiles and edge-kernel blocks of every
+ * handle, split into one segment per XCD of equal estimated cost, longest
+ * items first (block b of the launch runs item b / 8 of segment b % 8); then
+ * one launch injects every point source (a single larger handle runs as
+ * sbp_step runs it).  Per step one launch records every receiver.  Where the
+ * kernels use no scratch memory each step is a replay of a graph captured for
+ * the call (even and odd steps); otherwise the same launches are issued
+ * directly.  The source-time factors come from a device table uploaded every
+ * 64 steps.
+ * The work list uses 8-row tiles and one s-chunk length for the batch (from
  * sbp_autotune_batch, else a cost model); the handles' own launch settings
- * are restored on return.  With plain addressing on any handle
+ * are restored on return.  With plain addressing on any of its handles
  * (sbp_set_addressing), or with a handle of an order the work-list kernel
  * does not serve (order 8; orders 7 and 8 in SBP_F64), one stage and one
- * edge launch per interior order replace the work-list launch.  Each handle's state, time, step count and
- * receiver traces end up as after sbp_step(hs[i], nsteps, dt[i]), to
- * rounding (the batched kernels are separate instantiations of the same
- * kernel bodies).  All handles need the same dtype and the same stream,
- * distinct handles and a medium; the argument tables and the work list
- * (at most 65536 items) live in hs[0]'s workspace.  Synchronises the
- * stream before returning.
+ * edge launch per interior order replace the work-list launch.  Each handle's
+ * state, time, step count and receiver traces end up as after
+ * sbp_step(hs[i], nsteps, dt[i]), to rounding (the batched kernels are
+ * separate instantiations of the same kernel bodies).  All handles need the
+ * same dtype and the same stream, distinct handles and a medium; the argument
+ * tables and the work list (at most 65536 items) live in the workspace of the
+ * first handle of each group.  Synchronises the stream before returning.
  */
 int sbp_step_batch(sbp_handle* hs, int n, int nsteps, const double* dt);
 
 /*
- * Launch-shape autotuner of sbp_step_batch: times `reps` batched
- * right-hand-side launches (the work-list launch over every handle's tiles;
- * they write only the Runge-Kutta registers and the second state buffers,
+ * Launch-shape autotuner of sbp_step_batch's work list: times `reps` batched
+ * right-hand-side launches (the work-list launch over the tiles of every
+ * handle that sbp_step_batch would run over it, or of all handles if that is
+ * at most one; they write only the Runge-Kutta registers and the second state buffers,
  * so the states are untouched) for the cost model's s-chunk length and a few
  * others, and keeps the fastest for later sbp_step_batch calls of these
  * handles.  Writes the chosen length and its time per launch (ms) to the

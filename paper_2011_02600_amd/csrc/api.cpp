@@ -58,7 +58,7 @@ constexpr int kMaxRec = 65536;
 constexpr int kMaxBatch = 64;
 constexpr int kBatchTabSteps = 64;
 constexpr int kMaxItems = 65536;
-constexpr int kMaxGroups = 6;  // six orders
+constexpr int kMaxGroups = 7;  // seven orders
 
 constexpr int kMaxPart = 1024;
 constexpr double kPi = 3.14159265358979323846;
@@ -582,14 +582,10 @@ SourceArgs<T> source_args(sbp_ctx* h, int k, double dt, double tstage, bool rhs_
   return s;
 }
 
-// single precision: the point sources of stage k go into the stage and edge
-// kernels' update (StageArgs::nsrc and src_*), in place of a source_kernel
-// launch; returns whether they did
+// the point sources of stage k go into the stage and edge kernels' update
+// (StageArgs::nsrc and src_*), in place of a source_kernel launch
 template <typename T>
-bool fuse_sources(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, bool rhs_only,
-                  const StepClock* clock) {
-  a.nsrc = 0;
-  if ((sizeof(T) != 4 && !use_tile(h)) || h->src.empty()) return false;
+void put_sources(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, bool rhs_only, const StepClock* clock) {
   const SourceArgs<T> s = source_args<T>(h, k, dt, tstage, rhs_only, nullptr);
   a.nsrc = (int)h->src.size();
   a.src_w = s.width;
@@ -602,6 +598,14 @@ bool fuse_sources(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, 
   }
   a.src_wm = s.wm;
   a.src_clock = clock;
+}
+// returns whether they did (in double precision the tile kernel's only)
+template <typename T>
+bool fuse_sources(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, bool rhs_only,
+                  const StepClock* clock) {
+  a.nsrc = 0;
+  if ((sizeof(T) != 4 && !use_tile(h)) || h->src.empty()) return false;
+  put_sources<T>(h, a, k, dt, tstage, rhs_only, clock);
   return true;
 }
 
@@ -924,6 +928,7 @@ int batch_items(sbp_ctx** hs, int n, std::vector<BatchItem>& items, std::vector<
 // 5 stages x 2 parities), receiver arguments (2 step parities).
 template <typename T>
 struct BatchPlan {
+  bool tile = false;     // the tile kernel, one launch per order
   bool worklist = true;  // one launch over the work list (else one per order)
   unsigned orders = 0;   // bit o: interior order o present
   int maxseg = 0;        // longest work-list segment
@@ -947,7 +952,7 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
     buf_ok = buf_ok && !a.plain && 12.0 * (double)a.field * sizeof(T) < 4294967296.0;
     buf_ok = buf_ok && worklist_order_ok<T>(hs[g]->order);
   }
-  P.worklist = buf_ok;
+  P.worklist = buf_ok && !P.tile;
   P.n = n;
   P.orders = 0;
   for (int g = 0; g < n; ++g) P.orders |= 1u << hs[g]->order;
@@ -963,8 +968,15 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
     a.eqc = nullptr;
     a.nsrc = 0;
     for (int k = 0; k < 5; ++k)
-      for (int p = 0; p < 2; ++p)
-        sa[(std::size_t)(k * 2 + p) * kMaxBatch + g] = stage_entry<T>(h, a, k, h->cur ^ p, dt[g], rhs_only);
+      for (int p = 0; p < 2; ++p) {
+        StageArgs<T> e = stage_entry<T>(h, a, k, h->cur ^ p, dt[g], rhs_only);
+        if (P.tile) {
+          put_sources<T>(h, e, k, dt[g], 0.0, rhs_only, (const StepClock*)(base + R.clock));
+          e.src_stride = n * kMaxSources;
+          e.src_off = g * kMaxSources;
+        }
+        sa[(std::size_t)(k * 2 + p) * kMaxBatch + g] = e;
+      }
   }
   // wait for work of an earlier call that may still read the tables
   HIPCHK(hipStreamSynchronize(st));
@@ -1006,7 +1018,7 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
         const StageArgs<T> a = stage_args<T>(hs[P.ord[q]]);
         fs[q - P.gstart[G]] = ts;
         fe[q - P.gstart[G]] = te;
-        ts += a.ntiles;
+        ts += P.tile ? a.tile.ntiles : a.ntiles;
         te += edge_blocks(a);
       }
       fs[P.gstart[G + 1] - P.gstart[G]] = ts;
@@ -1017,8 +1029,10 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
     HIPCHK(hipMemcpyAsync(base + R.first, firsts.data(), firsts.size() * sizeof(int), hipMemcpyHostToDevice, st));
   }
   // boundary penalties: surface nodes of every grid, in the order of the
-  // stage argument table
-  {
+  // stage argument table (the tile kernel adds its own)
+  if (P.tile) {
+    HIPCHK(hipStreamSynchronize(st));
+  } else {
     std::vector<int> pfirst(n + 1, 0);
     for (int q = 0; q < n; ++q) {
       const sbp_ctx* h = hs[P.worklist ? q : P.ord[q]];
@@ -1112,6 +1126,17 @@ int batch_stage_launch(sbp_ctx** hs, const BatchPlan<T>& P, int k, int e, hipStr
     return batch_penalty_launch<T>(hs, P, dsa, st);
   }
   const int* dfirst = (const int*)(base + R.first);
+  if (P.tile) {
+    for (int G = 0; G < P.ngroups; ++G) {
+      BatchArgs<T> b{};
+      b.args = dsa + P.gstart[G];
+      b.n = P.gstart[G + 1] - P.gstart[G];
+      b.first = dfirst + (std::size_t)(2 * G) * (kMaxBatch + 1);
+      b.total = P.sblocks[G];
+      HIPCHK(launch_tile_batch<T>(hs[P.ord[P.gstart[G]]]->order, b, st));
+    }
+    return SBP_OK;
+  }
   for (int G = 0; G < P.ngroups; ++G) {
     BatchArgs<T> b{};
     b.args = dsa + P.gstart[G];
@@ -1140,7 +1165,7 @@ int batch_step_launches(sbp_ctx** hs, const BatchPlan<T>& P, int par, hipStream_
     const int e = k * 2 + ((par + k) & 1);
     int rc = batch_stage_launch<T>(hs, P, k, e, st);
     if (rc) return rc;
-    if (P.nsrc > 0) {
+    if (P.nsrc > 0 && !P.tile) {
       SourceBatch<T> sb{};
       sb.args = (const SourceArgs<T>*)(base + R.src) + (std::size_t)e * kMaxBatch;
       sb.first = (const int*)(base + R.src_first);
@@ -1162,26 +1187,33 @@ int batch_step_launches(sbp_ctx** hs, const BatchPlan<T>& P, int par, hipStream_
   return SBP_OK;
 }
 
-// Several handles advanced together.  Per Runge-Kutta stage one launch
+// Several handles advanced together.  Per Runge-Kutta stage the tile kernel
+// runs once per interior order over every grid's tiles (tile), or one launch
 // covers the stage tiles and edge blocks of every grid (a work list cut into
 // one segment per XCD, longest items first; with plain addressing, one stage
 // and one edge launch per interior order), then one launch injects every
-// source; per step one launch records every receiver.  In FP32 each step is
-// a replay of one of two graphs captured for the call (even and odd steps;
-// the argument tables hold both ping-pong parities); the per-step values
-// come from a device clock and a source-time table uploaded every
-// kBatchTabSteps steps.  Results agree with do_steps to rounding (the bodies
-// are the same, instantiated in another kernel).
+// source; per step one launch records every receiver.  Where the kernels use
+// no scratch memory each step is a replay of one of two graphs captured for
+// the call (even and odd steps; the argument tables hold both ping-pong
+// parities); the per-step values come from a device clock and a source-time
+// table uploaded every kBatchTabSteps steps.  Results agree with do_steps to
+// rounding (the bodies are the same, instantiated in another kernel).
 template <typename T>
-int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
+int do_steps_group(sbp_ctx** hs, int n, int nsteps, const double* dt, bool tile) {
   sbp_ctx* h0 = hs[0];
   hipStream_t st = h0->stream;
   const BatchRegion R = batch_region();
   char* base = h0->ws + h0->off_batch;
-  BatchSettings keep(hs, n);
-  int rc = batch_apply_L(hs, n, h0->batch_L);
+  BatchSettings keep(hs, tile ? 0 : n);
+  int rc = SBP_OK;
+  if (tile) {
+    for (int g = 0; g < n && !rc; ++g) rc = prepare_bounds(hs[g]);
+  } else {
+    rc = batch_apply_L(hs, n, h0->batch_L);
+  }
   if (rc) return rc;
   BatchPlan<T> P;
+  P.tile = tile;
   if ((rc = batch_upload<T>(hs, n, dt, false, P))) return rc;
   if (!h0->btab_host) {
     HIPCHK(hipHostMalloc((void**)&h0->btab_host, 2 * R.gtab_part, hipHostMallocDefault));
@@ -1201,7 +1233,9 @@ int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
   } drop{gx};
   // graphs replay only batched steps whose kernels use no scratch memory
   // (the FP32 kernels), as in do_steps
-  const bool use_graph = h0->graphs && P.worklist && batch_step_scratch<T>(P.orders) == 0;
+  bool use_graph = h0->graphs && (P.tile || (P.worklist && batch_step_scratch<T>(P.orders) == 0));
+  for (int o = 2; o <= 8 && P.tile; ++o)
+    if ((P.orders >> o) & 1u) use_graph = use_graph && tile_scratch<T>(o) == 0;
   if (use_graph) {
     if (!h0->cap) HIPCHK(hipStreamCreateWithFlags(&h0->cap, hipStreamNonBlocking));
     for (int par = 0; par < 2 && par < nsteps; ++par) {
@@ -1263,12 +1297,78 @@ int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
   return SBP_OK;
 }
 
+// whether a grid of a batch runs in a tile-kernel group (as use_tile; a
+// batch does not use the handles' own launch shapes)
+bool batch_tile(const sbp_ctx* h) { return !h->plain && h->g.n <= kTileNodes; }
+
+// A batch's grids are independent, so it runs in groups, each all its steps
+// before the next group's: grids the tile kernel serves in groups of at most
+// kGroupBytes of fields (39 per node and value), so that a group's fields stay
+// in the 256 MB memory-side cache from stage to stage; all larger grids
+// together over the work list (a single one as sbp_step would).
+// us per stage of 16 shots of 64^3, order 4, with the work list and in groups
+// of 1, 2, 3, 4, 6, 8 and 16: single precision 289, and 355, 286, 258, 233,
+// 258, 294, 288; double 562, and 570, 476, 469, 538, 532, 520, 507.  Eight
+// cubes of 65 to 129 points: 632 and 577; 16 of 33^3: 103 and 37.
+constexpr double kGroupBytes = 200e6;
+
+template <typename T>
+int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
+  const std::size_t cap = (std::size_t)(kGroupBytes / (39.0 * sizeof(T)));
+  std::vector<int> small, large;
+  for (int g = 0; g < n; ++g) (batch_tile(hs[g]) ? small : large).push_back(g);
+  std::stable_sort(small.begin(), small.end(), [&](int a, int b) { return hs[a]->g.n < hs[b]->g.n; });
+  std::vector<sbp_ctx*> gh;
+  std::vector<double> gd;
+  std::size_t nodes = 0;
+  auto run = [&](bool tile) -> int {
+    int rc = SBP_OK;
+    if (gh.empty()) return rc;
+    if (!tile && gh.size() == 1 && !gh[0]->plain) {
+      rc = do_steps<T>(gh[0], nsteps, gd[0]);
+      if (!rc) HIPCHK(hipStreamSynchronize(gh[0]->stream));
+    } else {
+      rc = do_steps_group<T>(gh.data(), (int)gh.size(), nsteps, gd.data(), tile);
+    }
+    gh.clear();
+    gd.clear();
+    nodes = 0;
+    return rc;
+  };
+  for (int g : small) {
+    if (!gh.empty() && nodes + hs[g]->g.n > cap) {
+      const int rc = run(true);
+      if (rc) return rc;
+    }
+    gh.push_back(hs[g]);
+    gd.push_back(dt[g]);
+    nodes += hs[g]->g.n;
+  }
+  int rc = run(true);
+  if (rc) return rc;
+  for (int g : large) {
+    gh.push_back(hs[g]);
+    gd.push_back(dt[g]);
+  }
+  return run(false);
+}
+
 // Batch launch-shape autotuner: times `reps` right-hand-side evaluations of
 // every grid (one batched stage launch each; they write only the
 // Runge-Kutta registers and the second state buffers) for the cost model's
 // chunk length and a few others, and keeps the fastest in every handle.
 template <typename T>
 int do_autotune_batch(sbp_ctx** hs, int n, int reps, int* bestL, double* best_ms) {
+  // the handles sbp_step_batch runs over the work list, if there are several
+  std::vector<sbp_ctx*> large;
+  for (int g = 0; g < n; ++g)
+    if (!batch_tile(hs[g])) large.push_back(hs[g]);
+  sbp_ctx** const all = hs;
+  const int nall = n;
+  if (large.size() > 1) {
+    hs = large.data();
+    n = (int)large.size();
+  }
   sbp_ctx* h0 = hs[0];
   hipStream_t st = h0->stream;
   const BatchRegion R = batch_region();
@@ -1315,7 +1415,7 @@ int do_autotune_batch(sbp_ctx** hs, int n, int reps, int* bestL, double* best_ms
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
-  for (int g = 0; g < n; ++g) hs[g]->batch_L = bL;
+  for (int g = 0; g < nall; ++g) all[g]->batch_L = bL;
   if (bestL) *bestL = bL;
   if (best_ms) *best_ms = best;
   return SBP_OK;
@@ -2249,15 +2349,18 @@ int sbp_profile(sbp_handle h, double* stage_ms, double* edge_ms, long long* nsta
 int sbp_destroy(sbp_handle h) {
   if (!h) return SBP_OK;
   // work still queued may read the staging buffer and the graphs
-  if (h->tab_host || h->gx[0] || h->gx[1]) (void)hipStreamSynchronize(h->stream);
+  if (h->tab_host || h->btab_host || h->gx[0] || h->gx[1]) (void)hipStreamSynchronize(h->stream);
   for (int e = 0; e < 3; ++e)
     if (h->ev[e]) (void)hipEventDestroy(h->ev[e]);
   for (int p = 0; p < kTabParts; ++p)
     if (h->tab_ev[p]) (void)hipEventDestroy(h->tab_ev[p]);
+  for (int p = 0; p < 2; ++p)
+    if (h->btab_ev[p]) (void)hipEventDestroy(h->btab_ev[p]);
   for (int c = 0; c < 2; ++c)
     if (h->gx[c]) (void)hipGraphExecDestroy(h->gx[c]);
   if (h->cap) (void)hipStreamDestroy(h->cap);
   if (h->tab_host) (void)hipHostFree(h->tab_host);
+  if (h->btab_host) (void)hipHostFree(h->btab_host);
   delete h;
   return SBP_OK;
 }

@@ -1169,17 +1169,6 @@ __global__ __launch_bounds__(64 * KZ) void edge_penalty_kernel(const StageArgs<T
   }
 }
 
-// last entry of first[0 .. n-1] (non-decreasing, first[0] = 0) that is <= item
-__device__ __forceinline__ int batch_find(const int* __restrict__ first, int n, int item) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (first[mid] <= item) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
 template <typename T, int ORDER, int TY, bool BUF>
 __global__ __launch_bounds__(64 * TY, SBP_STAGE_MIN_WAVES) void stage_kernel_batch(const BatchArgs<T> B) {
   const int per = gridDim.x >> 3;

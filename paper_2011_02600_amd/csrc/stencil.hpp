@@ -180,6 +180,17 @@ __device__ __forceinline__ void source_add(const StageArgs<T>& A, int i, int j, 
   }
 }
 
+// several grids in one launch: last entry of first[0 .. n-1] (non-decreasing, first[0] = 0) that is <= item
+__device__ __forceinline__ int batch_find(const int* __restrict__ first, int n, int item) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= item) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
 constexpr std::size_t kLdsBytes = 160 * 1024;
 
 }  // namespace sbp

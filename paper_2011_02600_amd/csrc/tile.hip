@@ -69,12 +69,15 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
   const TileShape& G = A.tile;
   if (tile >= G.ntiles) return;
   const int nq = A.nq, nr = A.nr, ns = A.ns;
+  // (read here, before the barrier, where arguments in memory are scalar loads)
+  const T ihq = A.inv_h[0], ihr = A.inv_h[1], ihs = A.inv_h[2], dt = A.dt, Ak = A.Ak, Bk = A.Bk;
+  const int sat = A.sat, nsrc = A.nsrc, read_dq = A.read_dq, ey = A.ey;
   // tile order: q fastest, then s, then r
   const int xt = tile % G.q.T, ks = tile / G.q.T;
   const int k = ks % ns, yt = ks / ns;
   const int x0 = G.q.start(xt), x1 = G.q.start(xt + 1);
   const int y0 = G.r.start(yt), y1 = G.r.start(yt + 1);
-  if (G.part == 2 && x1 < nq && y1 <= nr - A.ey) return;
+  if (G.part == 2 && x1 < nq && y1 <= nr - ey) return;
   const int w = x1 - x0, h = y1 - y0;
   const bool yfirst = y0 == 0, ylast = y1 == nr;
 
@@ -292,7 +295,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
       }
     }
   }
-  const bool act = G.part == 0 || (((unsigned)i < nqm && j < nr - A.ey) == (G.part == 1));
+  const bool act = G.part == 0 || (((unsigned)i < nqm && j < nr - ey) == (G.part == 1));
   if (!own || !act) return;
 
   // ---- what the update needs (double precision, orders 6 to 8: loaded where
@@ -303,7 +306,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
 #pragma unroll
     for (int c = 0; c < 3; ++c) mat[c] = gc.ld(9 + c, o);
     if constexpr (MODE == 0) {
-      const unsigned od = A.read_dq ? o : 0u;
+      const unsigned od = read_dq ? o : 0u;
 #pragma unroll
       for (int c = 0; c < 9; ++c) dqo[c] = gd.ld(c, od);
     }
@@ -341,8 +344,8 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
         sp += (WREG ? cp[WREG ? t : 0] : wp[t]) * tv[c * PX + t];
         sm += (WREG ? cm[WREG ? t : 0] : wm[t]) * tf[c * PX + t];
       }
-      u[0][c] = sp * A.inv_h[0];
-      dv[c] = sm * A.inv_h[0];
+      u[0][c] = sp * ihq;
+      dv[c] = sm * ihq;
       sched_fence<T>();
     }
   }
@@ -359,8 +362,8 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
           sp += T(S::a[s]) * lv[((s - R) * 3 + c) * PX];
           sm += T(S::a[s]) * lr[((R - s) * 3 + c) * RX];
         }
-        u[1][c] = sp * A.inv_h[1];
-        dv[c] -= sm * A.inv_h[1];
+        u[1][c] = sp * ihr;
+        dv[c] -= sm * ihr;
         sched_fence<T>();
       }
     } else {
@@ -379,15 +382,15 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
           sp += wp[t] * tv[(t * 3 + c) * PX];
           sm += wm[t] * tf[(t * 3 + c) * RX];
         }
-        u[1][c] = sp * A.inv_h[1];
-        dv[c] += sm * A.inv_h[1];
+        u[1][c] = sp * ihr;
+        dv[c] += sm * ihr;
         sched_fence<T>();
       }
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      u[2][c] = us[c] * A.inv_h[2];
-      dv[c] += fs[c] * A.inv_h[2];
+      u[2][c] = us[c] * ihs;
+      dv[c] += fs[c] * ihs;
     }
   }
 
@@ -396,30 +399,32 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
   node_rates(u, dv, mq, mr, me.m, mat[0], mat[1], mat[2], rate);
   // the penalties of the node's faces (one per axis at most)
   auto face = [&](int ax, bool hi, std::size_t idx) {
-    const T* p = A.face + (hi ? A.face_off[2 * ax + 1] : A.face_off[2 * ax]) + idx;
+    const std::size_t f0 = A.face_off[2 * ax], f1 = A.face_off[2 * ax + 1];
+    const T* p = A.face + (hi ? f1 : f0) + idx;
     const std::size_t n = A.face_n[2 * ax];
     T fc[kNumFaceCoef];
 #pragma unroll
     for (int c = 0; c < kNumFaceCoef; ++c) fc[c] = p[c * n];
-    const T g = hi ? A.gamma[2 * ax + 1] : A.gamma[2 * ax];
-    const bool tr = (hi ? A.traction[2 * ax + 1] : A.traction[2 * ax]) != 0;
+    const T g0 = A.gamma[2 * ax], g1 = A.gamma[2 * ax + 1], g = hi ? g1 : g0;
+    const int t0 = A.traction[2 * ax], t1 = A.traction[2 * ax + 1];
+    const bool tr = (hi ? t1 : t0) != 0;
     face_penalty(fc, g, hi ? T(1) : T(-1), tr, me.v, me.s, rate);
   };
-  if (A.sat) {
+  if (sat) {
     if (i == 0 || i == nq - 1) face(0, i != 0, (std::size_t)k * nr + j);
     if (j == 0 || j == nr - 1) face(1, j != 0, (std::size_t)k * nq + i);
     if (k == 0 || k == ns - 1) face(2, k != 0, (std::size_t)j * nq + i);
   }
   T sadd[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-  if (A.nsrc > 0) source_add(A, i, j, k, sadd);
+  if (nsrc > 0) source_add(A, i, j, k, sadd);
 #pragma unroll
   for (int c = 0; c < 9; ++c) {
-    T d = A.dt * rate[c];
-    if constexpr (MODE == 0) d += A.Ak * (A.read_dq ? dqo[c] : T(0));
+    T d = dt * rate[c];
+    if constexpr (MODE == 0) d += Ak * (read_dq ? dqo[c] : T(0));
     if (c >= 3) d += sadd[c >= 3 ? c - 3 : 0];
     // (kept in the caches: the next stage reads them)
     gd.template stp<0>(c, o, d);
-    if constexpr (MODE == 0) go.template stp<0>(c, o, (c < 3 ? me.v[c < 3 ? c : 0] : me.s[c < 3 ? 0 : c - 3]) + A.Bk * d);
+    if constexpr (MODE == 0) go.template stp<0>(c, o, (c < 3 ? me.v[c < 3 ? c : 0] : me.s[c < 3 ? 0 : c - 3]) + Bk * d);
   }
 }
 
@@ -429,6 +434,25 @@ __global__ __launch_bounds__(kTileNT, sizeof(T) == 4 && ORDER <= 6 ? 3 : 2) void
   // consecutive tiles on the same XCD
   const int per = gridDim.x >> 3;
   tile_body<T, ORDER, MODE>(A, (blockIdx.x & 7) * per + (blockIdx.x >> 3), lds);
+}
+
+// the tiles of several grids (a Runge-Kutta stage)
+template <typename T, int ORDER>
+__global__ __launch_bounds__(kTileNT, sizeof(T) == 4 && ORDER <= 6 ? 3 : 2) void tile_kernel_batch(
+    const BatchArgs<T> B) {
+  __shared__ __align__(16) char lds[TileLds<T, ORDER>::bytes];
+  const int per = gridDim.x >> 3;
+  const int item = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (item >= B.total) return;
+  const int g = batch_find(B.first, B.n, item);
+  const StageArgs<T>& A = B.args[g];
+  tile_body<T, ORDER, 0>(A, item - B.first[g], lds);
+}
+
+template <typename T, int ORDER>
+hipError_t launch_bt(const BatchArgs<T>& b, hipStream_t st) {
+  hipLaunchKernelGGL((tile_kernel_batch<T, ORDER>), dim3((b.total + 7) / 8 * 8), dim3(kTileNT), 0, st, b);
+  return hipGetLastError();
 }
 
 template <typename T, int ORDER>
@@ -445,7 +469,8 @@ template <typename T, int ORDER>
 std::size_t scratch_t() {
   std::size_t m = 0;
   const void* fns[] = {reinterpret_cast<const void*>(&tile_kernel<T, ORDER, 0>),
-                       reinterpret_cast<const void*>(&tile_kernel<T, ORDER, 1>)};
+                       reinterpret_cast<const void*>(&tile_kernel<T, ORDER, 1>),
+                       reinterpret_cast<const void*>(&tile_kernel_batch<T, ORDER>)};
   for (const void* f : fns) {
     hipFuncAttributes at{};
     if (hipFuncGetAttributes(&at, f) != hipSuccess) return (std::size_t)-1;
@@ -471,6 +496,20 @@ hipError_t launch_tile(int order, int mode, const StageArgs<T>& a, hipStream_t s
 }
 
 template <typename T>
+hipError_t launch_tile_batch(int order, const BatchArgs<T>& b, hipStream_t st) {
+  switch (order) {
+    case 2: return launch_bt<T, 2>(b, st);
+    case 3: return launch_bt<T, 3>(b, st);
+    case 4: return launch_bt<T, 4>(b, st);
+    case 5: return launch_bt<T, 5>(b, st);
+    case 6: return launch_bt<T, 6>(b, st);
+    case 7: return launch_bt<T, 7>(b, st);
+    case 8: return launch_bt<T, 8>(b, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <typename T>
 std::size_t tile_scratch(int order) {
   switch (order) {
     case 2: return scratch_t<T, 2>();
@@ -486,9 +525,11 @@ std::size_t tile_scratch(int order) {
 
 #ifdef SBP_TILE_F64
 template hipError_t launch_tile<double>(int, int, const StageArgs<double>&, hipStream_t);
+template hipError_t launch_tile_batch<double>(int, const BatchArgs<double>&, hipStream_t);
 template std::size_t tile_scratch<double>(int);
 #else
 template hipError_t launch_tile<float>(int, int, const StageArgs<float>&, hipStream_t);
+template hipError_t launch_tile_batch<float>(int, const BatchArgs<float>&, hipStream_t);
 template std::size_t tile_scratch<float>(int);
 #endif
 

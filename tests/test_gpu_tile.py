@@ -72,3 +72,42 @@ def test_autotune_considers_the_tile_kernel():
     b = s.rhs()
     assert ms > 0 and torch.allclose(a, b, rtol=1e-4, atol=1e-4 * float(b.abs().max()))
     s.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_batch_of_small_and_large_grids(dtype):
+    """A batch of grids on both sides of the tile kernel's limit (a group of
+    small ones over two orders, several launches of a group, the larger ones
+    over the work list) against the same handles stepped one by one."""
+    from paper_2011_02600_amd import sbp
+    print("case: batch of small and large grids %s" % dtype, flush=True)
+    grids = [(4, (40, 33, 20)), (6, (121, 122, 120)), (6, (37, 65, 25)), (4, (33, 21, 128)), (4, (121, 121, 121)),
+             (3, (101, 99, 97))]
+
+    def solvers():
+        out = []
+        for n, (order, shape) in enumerate(grids):
+            ns, nr, nq = shape
+            s = sbp.Solver(W.warped_mesh(nq, nr, ns, seed=n, amp=0.02), order=order, dtype=dtype,
+                           gamma=[1, 0, 0.5, 0, -1, 1])
+            s.set_material(*W.random_medium(shape, 60 + n))
+            s.set_state(W.random_state(shape, 70 + n, smooth=True))
+            if n % 2 == 0:
+                s.add_source((0.31 + 0.05 * n, 0.5, 0.47), (0.2, 0.1, -0.3, 1.0, 0.0, 0.4), 0, 8.0, 0.05)
+            s.record([(1, 2, 3), (nq - 1, nr // 2, ns - 1)], 8)
+            out.append(s)
+        return out
+
+    dts = [1e-4 * (1 + 0.1 * n) for n in range(len(grids))]
+    alone, together = solvers(), solvers()
+    for s, d in zip(alone, dts):
+        s.step(5, d)
+    sbp.sbp_step_batch([s.h for s in together], 5, dts)
+    tol = 1e-5 if dtype == "f32" else 1e-12
+    for n, (a, b) in enumerate(zip(alone, together)):
+        e = rel_max(b.get_state().double().cpu().numpy(), a.get_state().double().cpu().numpy())
+        t = rel_max(b.traces.double().cpu().numpy().transpose(2, 0, 1), a.traces.double().cpu().numpy().transpose(2, 0, 1))
+        print("  grid %d: state %.1e traces %.1e" % (n, e, t), flush=True)
+        assert e <= tol and t <= tol and a.time() == b.time()
+    for s in alone + together:
+        s.close()
