@@ -22,6 +22,8 @@ extern "C" {
 
 enum { SBP_NN_OK = 0, SBP_NN_EINVAL = -1, SBP_NN_EHIP = -3 };
 enum { SBP_NN_MSE_PARTS = 256 };
+/* most blocks (rows of partial sums) of the line kernels below */
+enum { SBP_NN_LINE_BLOCKS = 1024 };
 
 /*
  * C[b] = alpha A[b] B[b] + beta C[b] for b < batch, A M x K, B K x N, C M x N,
@@ -102,6 +104,66 @@ int sbp_nn_axpy(long long n, float a, const float* x, float* y, void* stream);
 
 /* Text of the last failure on the calling thread. */
 const char* sbp_nn_last_error(void);
+
+/*
+ * Fused layers of the network on an n^3 grid (n <= 64, n a multiple of 4) with
+ * m <= 16 cosine modes per axis and C <= 64 channels; other shapes are
+ * SBP_NN_EINVAL and take the calls above.  basis: n x m.  A line is the C x n
+ * values of one (s, z, y).  t1 and i1 are (S, C, n, n, m) arrays: the x
+ * transform of an activation, and the spectral path before its inverse x
+ * transform.  Products as in sbp_nn_gemm, bit for bit its results.
+ */
+
+/* t1 = x transform of h_0 = wl[c] x + bl[c] */
+int sbp_nn_lift_modes(int S, int C, int n, int m, const float* basis, const float* x, const float* wl,
+                      const float* bl, float* t1, void* stream);
+/* out (SC, m, m, m) = y and z transforms of t1 (SC, n, n, m); t1 is overwritten */
+int sbp_nn_modes_forward(int SC, int n, int m, const float* basis, float* t1, float* out, void* stream);
+/* i1 (SC, n, n, m) = inverse z and y transforms of y (SC, m, m, m) */
+int sbp_nn_modes_inverse(int SC, int n, int m, const float* basis, const float* y, float* i1, void* stream);
+/*
+ * z = (inverse x transform of i1) + W h + bias, hn = gelu(z), t1 = x
+ * transform of hn; h NULL: h_0 from x, wl, bl.
+ */
+int sbp_nn_line_forward(int S, int C, int n, int m, const float* basis, const float* i1, const float* h,
+                        const float* x, const float* wl, const float* bl, const float* W, const float* bias, float* z,
+                        float* hn, float* t1, void* stream);
+/*
+ * f[s][r][c] = the last layer (no activation) at the receivers pos: inverse
+ * transforms of y (S, C, m, m, m) + W h + bias there.  S <= 65535.
+ */
+int sbp_nn_receiver_forward(int S, int C, int n, int m, int R, const float* basis, const float* y, const float* h,
+                            const float* W, const float* bias, const int* pos, float* f, void* stream);
+/*
+ * Backward of the last layer from df (S, R, C).  The U distinct receiver
+ * positions upos (sorted) have the receivers u_r[u_r0[u] .. u_r0[u+1]-1];
+ * line zy has the positions line_u0[zy] .. line_u0[zy+1]-1 (n^2 + 1 entries);
+ * lines: the nlines lines that have any.  dzu, hu (S, U, C): the summed df
+ * and h at the positions; gb: sum of dzu; t1: its x transform.
+ */
+int sbp_nn_receiver_backward(int S, int C, int n, int m, int R, int U, int nlines, const float* basis,
+                             const float* df, const float* h, const int* lines, const int* line_u0, const int* upos,
+                             const int* u_r0, const int* u_r, float* dzu, float* hu, float* gb, float* t1,
+                             void* stream);
+/*
+ * dh = (inverse x transform of i1) + W^T dz_next (or, dz_next NULL, + wdz
+ * (S, U, C) at the positions upos), dz = dh gelu'(z), t1 = x transform of dz,
+ * and partial sums of dz h^T (h NULL: h_0) and dz: C x C values and C values
+ * for each of at most SBP_NN_LINE_BLOCKS blocks, summed by sbp_nn_line_sums.
+ */
+int sbp_nn_line_backward(int S, int C, int n, int m, const float* basis, const float* i1, const float* dz_next,
+                         const float* W, int U, const int* line_u0, const int* upos, const float* wdz, const float* z,
+                         const float* h, const float* x, const float* wl, const float* bl, float* dz, float* t1,
+                         float* gw_part, double* gb_part, void* stream);
+int sbp_nn_line_sums(int S, int C, int n, const float* gw_part, const double* gb_part, float* gw, float* gb,
+                     void* stream);
+/*
+ * gw[c] = sum of dh x and gb[c] = sum of dh for dh = (inverse x transform of
+ * i1) + W^T dz0; part: 2 C doubles per block (at most SBP_NN_LINE_BLOCKS).
+ */
+int sbp_nn_lift_backward(int S, int C, int n, int m, const float* basis, const float* i1, const float* dz0,
+                         const float* W, const float* x, const float* wl, const float* bl, double* part, float* gw,
+                         float* gb, void* stream);
 
 #ifdef __cplusplus
 }

@@ -12,11 +12,15 @@
 #include <mutex>
 
 #include "../../include/sbp_nn.h"
+#include "nn_math.hpp"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using sbp_nn::bf16x4;
+using sbp_nn::bf16x8;
+using sbp_nn::f32x4;
+using sbp_nn::gelu;
+using sbp_nn::gelu_grad;
 
 // ---------------------------------------------------------------------------
 // C[b] = alpha op(A[b]) op(B[b]) + beta C[b] for M x N x K with arbitrary
@@ -50,7 +54,6 @@ struct GemmArgs {
 };
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // tile rows r0 .. r0+63 (m of A, n of B) x k0 .. k0+31 of an operand with
 // element strides s_row, s_k, R rows and K columns in all
@@ -212,18 +215,6 @@ void gemm_launch_b(int bm, dim3 grid, hipStream_t st, const GemmArgs& g) {
 }
 
 // ---------------------------------------------------------------------------
-// GELU, tanh form: gelu(z) = z/2 (1 + tanh(s (z + 0.044715 z^3))), s = sqrt(2/pi)
-__device__ __forceinline__ float gelu(float z) {
-  const float s = 0.7978845608028654f;
-  return 0.5f * z * (1.f + tanhf(s * (z + 0.044715f * z * z * z)));
-}
-__device__ __forceinline__ float gelu_grad(float z) {
-  const float s = 0.7978845608028654f;
-  const float u = s * (z + 0.044715f * z * z * z);
-  const float t = tanhf(u);
-  return 0.5f * (1.f + t) + 0.5f * z * (1.f - t * t) * s * (1.f + 3.f * 0.044715f * z * z);
-}
-
 __global__ void bias_act_kernel(int S, int C, long long P, const float* k, const float* u, const float* bias,
                                 float* z, float* h, int act) {
   const long long n = (long long)S * C * P;
@@ -475,6 +466,11 @@ int nn_status() {
 }
 
 }  // namespace
+
+namespace sbp_nn {
+int set_error(const char* msg) { return nn_fail(msg); }
+int status() { return nn_status(); }
+}  // namespace sbp_nn
 
 extern "C" {
 

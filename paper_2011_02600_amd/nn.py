@@ -52,6 +52,15 @@ def lib():
             "sbp_nn_mse_noalloc": [c_ll, c_void_p, c_void_p, c_void_p, c_float, P(ctypes.c_double), c_void_p],
             "sbp_nn_adam": [c_ll, c_void_p, c_void_p, c_void_p, c_void_p, c_float, c_float, c_float, c_float, c_int,
                             c_void_p],
+            "sbp_nn_lift_modes": [c_int] * 4 + [c_void_p] * 6,
+            "sbp_nn_modes_forward": [c_int] * 3 + [c_void_p] * 4,
+            "sbp_nn_modes_inverse": [c_int] * 3 + [c_void_p] * 4,
+            "sbp_nn_line_forward": [c_int] * 4 + [c_void_p] * 12,
+            "sbp_nn_receiver_forward": [c_int] * 5 + [c_void_p] * 8,
+            "sbp_nn_receiver_backward": [c_int] * 7 + [c_void_p] * 13,
+            "sbp_nn_line_backward": [c_int] * 4 + [c_void_p] * 4 + [c_int] + [c_void_p] * 13,
+            "sbp_nn_line_sums": [c_int] * 3 + [c_void_p] * 5,
+            "sbp_nn_lift_backward": [c_int] * 4 + [c_void_p] * 11,
             "sbp_nn_axpy": [c_ll, c_float, c_void_p, c_void_p, c_void_p],
         }
         for name, args in sig.items():
@@ -154,6 +163,22 @@ class SpectralOperator:
         self._part = torch.zeros(256, dtype=torch.float64, device=self.dev)
         self._cpart = torch.zeros(64 * width, dtype=torch.float64, device=self.dev)  # channel sums
         self._bufs = {}
+        # the shapes the fused layer kernels serve (include/sbp_nn.h); the last
+        # layer then exists at the receivers only
+        self.fused = n <= 64 and n % 4 == 0 and modes <= 16 and width <= 64 and layers >= 2
+        if self.fused:
+            self._receiver_tables(np.asarray(pos, dtype=np.int64))
+
+    def _receiver_tables(self, pos):
+        """Distinct receiver positions (sorted), the receivers of each, and
+        the positions of each line (z, y) of the grid, for the backward pass."""
+        n = self.n
+        upos, inv = np.unique(pos, return_inverse=True)
+        dev = lambda a: self.torch.tensor(np.asarray(a, dtype=np.int32), device=self.dev)
+        self._u = dict(count=len(upos), pos=dev(upos), r=dev(np.argsort(inv, kind="stable")),
+                       r0=dev(np.concatenate([[0], np.cumsum(np.bincount(inv, minlength=len(upos)))])),
+                       line0=dev(np.searchsorted(upos // n, np.arange(n * n + 1))),
+                       lines=dev(np.unique(upos // n)))
 
     # ---- buffers --------------------------------------------------------------
     def _buf(self, name, shape):
@@ -203,6 +228,9 @@ class SpectralOperator:
         p, st, lb = self.params, self.stream, lib()
         self.S = S
         self.x = x
+        self.was_fused = self._fits(S)
+        if self.was_fused:
+            return self._head(self._forward_fused(x), S)
         h = self._buf("h0", (S, C, P))
         _ck(lb.sbp_nn_lift(S, C, P, _p(x), _p(p["w_lift"]), _p(p["b_lift"]), _p(h), st))
         self.hs, self.zs, self.xh = [h], [], []
@@ -225,12 +253,52 @@ class SpectralOperator:
             h = hn
         f = self._buf("feat", (S, self.R, C))
         _ck(lb.sbp_nn_gather(S, C, P, self.R, _p(self.pos), _p(h), _p(f), st))
-        y = self._buf("y", (S, self.R, self.T))
-        R, T = self.R, self.T
+        return self._head(f, S)
+
+    def _head(self, f, S):
+        C, R, T = self.C, self.R, self.T
+        p, st, lb = self.params, self.stream, lib()
+        y = self._buf("y", (S, R, T))
         # per receiver r: y[:, r, :] (S x T) = f[:, r, :] (S x C) @ D[r] (C x T)
         gemm(f, p["D"], y, S, T, C, (C, R * C, 1), (C * T, T, 1), (T, R * T, 1), batch=R, stream=st)
         _ck(lb.sbp_nn_add_rows(S, self.R * self.T, _p(p["b_out"]), _p(y), st))
         return y
+
+    def _fits(self, S):
+        """Whether a batch of S media takes the fused layers: their shape, the
+        batch limit of the calls they replace, contiguous 16-byte rows of x."""
+        return self.fused and S > 0 and S * self.C * self.n <= 65535 and self.x.is_contiguous() \
+            and self.x.data_ptr() % 16 == 0
+
+    def _forward_fused(self, x):
+        """The layers as fused passes over the activations; returns the last
+        layer's values at the receivers.  h_0 is never formed (it is w x + b),
+        nor are the last layer's values away from the receivers."""
+        S, C, n, m, P, L = x.shape[0], self.C, self.n, self.m, self.P, self.L
+        p, st, lb, B = self.params, self.stream, lib(), _p(self.B)
+        lift = (_p(x), _p(p["w_lift"]), _p(p["b_lift"]))
+        t1 = self._buf("line1", (S * C, n, n, m))
+        i1 = self._buf("line2", (S * C, n, n, m))
+        yh = self._buf("yh", (S, C, m ** 3))
+        _ck(lb.sbp_nn_lift_modes(S, C, n, m, B, *lift, _p(t1), st))
+        self.hs, self.zs, self.xh = [None], [], []
+        for l in range(L):
+            xh = self._buf("xh%d" % l, (S, C, m ** 3))
+            _ck(lb.sbp_nn_modes_forward(S * C, n, m, B, _p(t1), _p(xh), st))
+            self._mix(p["R%d" % l], xh, S, yh)
+            self.xh.append(xh)
+            W, b = _p(p["W%d" % l]), _p(p["b%d" % l])
+            if l == L - 1:
+                break
+            _ck(lb.sbp_nn_modes_inverse(S * C, n, m, B, _p(yh), _p(i1), st))
+            z = self._buf("z%d" % l, (S, C, P))
+            hn = self._buf("h%d" % (l + 1), (S, C, P))
+            _ck(lb.sbp_nn_line_forward(S, C, n, m, B, _p(i1), _p(self.hs[l]), *lift, W, b, _p(z), _p(hn), _p(t1), st))
+            self.zs.append(z)
+            self.hs.append(hn)
+        f = self._buf("feat", (S, self.R, C))
+        _ck(lb.sbp_nn_receiver_forward(S, C, n, m, self.R, B, _p(yh), _p(self.hs[L - 1]), W, b, _p(self.pos), _p(f), st))
+        return f
 
     # ---- loss and backward ---------------------------------------------------
     def loss(self, y, target, scale=1.0):
@@ -252,6 +320,8 @@ class SpectralOperator:
         _ck(lb.sbp_nn_sum_rows(S, R * T, _p(dy), _p(g["b_out"]), 0, st))
         df = self._buf("dfeat", (S, R, C))
         gemm(dy, p["D"], df, S, C, T, (T, R * T, 1), (C * T, 1, T), (C, R * C, 1), batch=R, stream=st)
+        if self.was_fused:
+            return self._backward_fused(df)
         dh = self._buf("dh", (S, C, P))
         dh.zero_()
         _ck(lb.sbp_nn_scatter(S, C, P, R, _p(self.pos), _p(df), _p(dh), st))
@@ -278,6 +348,54 @@ class SpectralOperator:
         # lift: h0 = w x + b
         _ck(lb.sbp_nn_channel_sum(S, C, P, _p(dh), _p(self.x), _p(g["w_lift"]), 0, _p(self._cpart), st))
         _ck(lb.sbp_nn_channel_sum(S, C, P, _p(dh), None, _p(g["b_lift"]), 0, _p(self._cpart), st))
+
+    def _backward_fused(self, df):
+        """Backward pass of the layers from the gradient df (S, R, C) of the
+        last layer's values at the receivers: one pass over the activations
+        per layer."""
+        S, C, n, m, P, L, R = self.S, self.C, self.n, self.m, self.P, self.L, self.R
+        p, g, st, lb, B, m3 = self.params, self.grads, self.stream, lib(), _p(self.B), self.m ** 3
+        u = self._u
+        U = u["count"]
+        lift = (_p(self.x), _p(p["w_lift"]), _p(p["b_lift"]))
+        t1 = self._buf("line1", (S * C, n, n, m))
+        i1 = self._buf("line2", (S * C, n, n, m))
+        dyh = self._buf("dyh", (S, C, m3))
+        dxh = self._buf("dxh", (S, C, m3))
+        nb = 1024
+        gw_part = self._buf("gw_part", (nb, C, C))
+        gb_part = self._buf("gb_part", (nb, 2 * C, 2))  # doubles
+        # last layer: at the receivers
+        l = L - 1
+        dzu, hu, wdz = (self._buf(k, (S, U, C)) for k in ("dzu", "hu", "wdz"))
+        _ck(lb.sbp_nn_receiver_backward(S, C, n, m, R, U, u["lines"].numel(), B, _p(df), _p(self.hs[l]),
+                                        _p(u["lines"]), _p(u["line0"]), _p(u["pos"]), _p(u["r0"]), _p(u["r"]),
+                                        _p(dzu), _p(hu), _p(g["b%d" % l]), _p(t1), st))
+        parts = self._buf("wparts", (S, C, C))
+        gemm(dzu, hu, parts, C, C, U, (U * C, 1, C), (U * C, C, 1), (C * C, C, 1), batch=S, stream=st)
+        _ck(lb.sbp_nn_sum_rows(S, C * C, _p(parts), _p(g["W%d" % l]), 0, st))
+        gemm(dzu, p["W%d" % l], wdz, S * U, C, C, (0, C, 1), (0, C, 1), (0, C, 1), stream=st)
+        dz = None
+        while True:
+            # spectral path of layer l: dY = T(dz), dR_q = dY_q X_q^T, dX = R^T dY
+            _ck(lb.sbp_nn_modes_forward(S * C, n, m, B, _p(t1), _p(dyh), st))
+            gemm(dyh, self.xh[l], g["R%d" % l], C, C, S, (1, m3, C * m3), (1, C * m3, m3), (C * C, C, 1), batch=m3,
+                 stream=st)
+            self._mix(p["R%d" % l], dyh, S, dxh, transpose=True)
+            _ck(lb.sbp_nn_modes_inverse(S * C, n, m, B, _p(dxh), _p(i1), st))
+            W = _p(p["W%d" % l])
+            if l == 0:
+                break
+            l -= 1
+            out = self._buf("dz%d" % (l % 2), (S, C, P))
+            _ck(lb.sbp_nn_line_backward(S, C, n, m, B, _p(i1), _p(dz), W, U, _p(u["line0"]), _p(u["pos"]), _p(wdz),
+                                        _p(self.zs[l]), _p(self.hs[l]), *lift, _p(out), _p(t1), _p(gw_part),
+                                        _p(gb_part), st))
+            _ck(lb.sbp_nn_line_sums(S, C, n, _p(gw_part), _p(gb_part), _p(g["W%d" % l]), _p(g["b%d" % l]), st))
+            dz = out
+        # h0 = w x + b
+        _ck(lb.sbp_nn_lift_backward(S, C, n, m, B, _p(i1), _p(dz), W, *lift, _p(gb_part), _p(g["w_lift"]),
+                                    _p(g["b_lift"]), st))
 
     def _weight_grad(self, dz, h, out):
         """out (C x C) = sum_s dz_s h_s^T: the long contraction over the grid is
