@@ -12,51 +12,35 @@
 //   L^T l = -W L_v(W^{-1} l) + Bd W^{-1} l + P^T l,
 // P the face-local penalty blocks.  L_v(W^{-1} l) is one forward
 // right-hand-side evaluation with the penalties off (the stage kernel); the
-// kernels here apply W^{-1} (adj_pre), -W (adj_post, every node) and Bd and
-// P^T (adj_face, face nodes only, one launch per axis).
+// kernels here apply W^{-1} (pre_node), -W (stage_node) and Bd and P^T
+// (face_node, face nodes only).
 //
 // The material enters the right-hand side pointwise: 1/(rho J) times the
 // flux divergence dv, lambda/J and mu/J times the velocity gradient terms,
-// and the penalty coefficients of the node's faces.  adj_grad takes dv and
+// and the penalty coefficients of the node's faces.  stage_node takes dv and
 // the gradient terms from a forward evaluation with unit material
-// (lambda/J = 0, mu/J = 1, 1/(rho J) = 1, penalties off) and differentiates
-// the penalties on dual numbers.
+// (lambda/J = 0, mu/J = 1, 1/(rho J) = 1, penalties off); face_node
+// differentiates the penalties.
+//
+// Everything between two right-hand sides is local to a node: one launch
+// (adj_stage_kernel).  It reads and writes 73 words per node and is bound by
+// them: SP_F32 us a stage for 129^3 in single precision (the passes it replaces
+// took 256), SP_F64 for 33^3 in double (was 110), where the chain of the face
+// nodes counts.
 #include <hip/hip_runtime.h>
 
 #include "adjoint.hpp"
-#include "penalty.hpp"
 
 namespace sbp {
 namespace {
 
-// value and derivative along one direction
-template <typename T>
-struct Dual {
-  T v, d;
-  Dual() = default;
-  __device__ Dual(double x) : v(T(x)), d(T(0)) {}
-  __device__ Dual(T x, T dx) : v(x), d(dx) {}
-};
-template <typename T>
-__device__ __forceinline__ Dual<T> operator+(Dual<T> a, Dual<T> b) { return Dual<T>(a.v + b.v, a.d + b.d); }
-template <typename T>
-__device__ __forceinline__ Dual<T> operator-(Dual<T> a, Dual<T> b) { return Dual<T>(a.v - b.v, a.d - b.d); }
-template <typename T>
-__device__ __forceinline__ Dual<T> operator-(Dual<T> a) { return Dual<T>(-a.v, -a.d); }
-template <typename T>
-__device__ __forceinline__ Dual<T> operator*(Dual<T> a, Dual<T> b) {
-  return Dual<T>(a.v * b.v, a.d * b.v + a.v * b.d);
-}
-template <typename T>
-__device__ __forceinline__ Dual<T>& operator+=(Dual<T>& a, Dual<T> b) { return a = a + b; }
-template <typename T>
-__device__ __forceinline__ Dual<T>& operator-=(Dual<T>& a, Dual<T> b) { return a = a - b; }
-
+// (the weight is loaded by every node, also where it is 1: a branch around each
+// of the three loads puts their latencies in a row)
 template <typename T>
 __device__ __forceinline__ T norm_w(const AdjArgs<T>& A, int i, int n) {
-  if (i < A.m) return A.w[i];
-  if (i >= n - A.m) return A.w[n - 1 - i];
-  return T(1);
+  const int e = min(i, n - 1 - i);
+  const T w = A.w[min(e, kMaxM - 1)];
+  return e < A.m ? w : T(1);
 }
 
 struct Node {
@@ -64,11 +48,12 @@ struct Node {
   long long o;
 };
 
+// (a grid of 2^32 nodes does not fit the memory)
 template <typename T>
-__device__ __forceinline__ Node node_of(const AdjArgs<T>& A, long long n) {
+__device__ __forceinline__ Node node_of(const AdjArgs<T>& A, unsigned n) {
   Node d;
   d.i = (int)(n % A.nq);
-  const long long t = n / A.nq;
+  const unsigned t = n / A.nq;
   d.j = (int)(t % A.nr);
   d.k = (int)(t / A.nr);
   d.o = A.nm(d.i, d.j, d.k);
@@ -76,210 +61,280 @@ __device__ __forceinline__ Node node_of(const AdjArgs<T>& A, long long n) {
 }
 
 template <typename T>
+__host__ __device__ __forceinline__ unsigned surface_nodes(const AdjArgs<T>& A) {
+  return 2u * (unsigned)A.nq * A.nr + 2u * (unsigned)A.nq * (A.ns - 2) + 2u * (unsigned)(A.nr - 2) * (A.ns - 2);
+}
+
+// d = a dqb + b qb (dqb: its 9 values), y = W^{-1} d; both stored
+template <typename T>
+__device__ __forceinline__ void pre_node(const AdjArgs<T>& A, const Node& nd, const T dqb[9], const T qb[9], T lamJ,
+                                         T muJ, T rJ) {
+  const std::size_t F = A.field;
+  const long long o = nd.o;
+  T d[9];
+#pragma unroll
+  for (int c = 0; c < 9; ++c) {
+    const T prev = A.a != T(0) ? A.a * dqb[c] : T(0);
+    d[c] = prev + A.b * qb[c];
+    A.dqb[c * F + o] = d[c];
+  }
+  const T iH = T(1) / (A.h[0] * norm_w(A, nd.i, A.nq) * A.h[1] * norm_w(A, nd.j, A.nr) * A.h[2] *
+                       norm_w(A, nd.k, A.ns));
+  // W^{-1}: v / (H rho J), and C / (H J) on the stress (engineering shear)
+  const T tr = d[3] + d[4] + d[5];
+  T y[9];
+  y[0] = rJ * d[0] * iH;
+  y[1] = rJ * d[1] * iH;
+  y[2] = rJ * d[2] * iH;
+  y[3] = (lamJ * tr + T(2) * muJ * d[3]) * iH;
+  y[4] = (lamJ * tr + T(2) * muJ * d[4]) * iH;
+  y[5] = (lamJ * tr + T(2) * muJ * d[5]) * iH;
+  y[6] = muJ * d[6] * iH;
+  y[7] = muJ * d[7] * iH;
+  y[8] = muJ * d[8] * iH;
+#pragma unroll
+  for (int c = 0; c < 9; ++c) A.y[c * F + o] = y[c];
+}
+
+template <typename T>
 __global__ void adj_pre_kernel(const AdjArgs<T> A) {
-  const long long N = (long long)A.nq * A.nr * A.ns;
+  const unsigned N = (unsigned)A.nq * A.nr * A.ns;
   const std::size_t F = A.field;
-  for (long long n = blockIdx.x * (long long)blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
+  for (unsigned n = blockIdx.x * blockDim.x + threadIdx.x; n < N; n += gridDim.x * blockDim.x) {
     const Node nd = node_of(A, n);
     const long long o = nd.o;
-    T d[9];
+    T l[9], qb[9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) {
-      const T prev = A.a != T(0) ? A.a * A.dqb[c * F + o] : T(0);
-      d[c] = prev + A.b * A.qb[c * F + o];
-      A.dqb[c * F + o] = d[c];
+      l[c] = A.a != T(0) ? A.dqb[c * F + o] : T(0);
+      qb[c] = A.qb[c * F + o];
     }
-    const T iH = T(1) / (A.h[0] * norm_w(A, nd.i, A.nq) * A.h[1] * norm_w(A, nd.j, A.nr) * A.h[2] *
-                         norm_w(A, nd.k, A.ns));
-    const T lamJ = A.coef[9 * F + o], muJ = A.coef[10 * F + o], rJ = A.coef[11 * F + o];
-    // W^{-1}: v / (H rho J), and C / (H J) on the stress (engineering shear)
-    const T tr = d[3] + d[4] + d[5];
-    T y[9];
-    y[0] = rJ * d[0] * iH;
-    y[1] = rJ * d[1] * iH;
-    y[2] = rJ * d[2] * iH;
-    y[3] = (lamJ * tr + T(2) * muJ * d[3]) * iH;
-    y[4] = (lamJ * tr + T(2) * muJ * d[4]) * iH;
-    y[5] = (lamJ * tr + T(2) * muJ * d[5]) * iH;
-    y[6] = muJ * d[6] * iH;
-    y[7] = muJ * d[7] * iH;
-    y[8] = muJ * d[8] * iH;
-#pragma unroll
-    for (int c = 0; c < 9; ++c) A.y[c * F + o] = y[c];
+    pre_node(A, nd, l, qb, A.coef[9 * F + o], A.coef[10 * F + o], A.coef[11 * F + o]);
   }
 }
 
-template <typename T>
-__global__ void adj_post_kernel(const AdjArgs<T> A) {
-  const long long N = (long long)A.nq * A.nr * A.ns;
-  const std::size_t F = A.field;
-  for (long long n = blockIdx.x * (long long)blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
-    const Node nd = node_of(A, n);
-    const long long o = nd.o;
-    const T wq = norm_w(A, nd.i, A.nq), wr = norm_w(A, nd.j, A.nr), ws = norm_w(A, nd.k, A.ns);
-    const T Hn = A.h[0] * wq * A.h[1] * wr * A.h[2] * ws;
-    const T lamJ = A.coef[9 * F + o], muJ = A.coef[10 * F + o], rJ = A.coef[11 * F + o];
-    T r[9], out[9];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) r[c] = A.r[c * F + o];
-    // -W r: -H rho J r_v and -H J C^{-1} r_sigma
-    out[0] = -Hn * r[0] / rJ;
-    out[1] = -Hn * r[1] / rJ;
-    out[2] = -Hn * r[2] / rJ;
-    const T trr = r[3] + r[4] + r[5];
-    const T cl = lamJ / (T(3) * lamJ + T(2) * muJ);
-    const T i2m = T(1) / (T(2) * muJ);
-    out[3] = -Hn * (r[3] - cl * trr) * i2m;
-    out[4] = -Hn * (r[4] - cl * trr) * i2m;
-    out[5] = -Hn * (r[5] - cl * trr) * i2m;
-    out[6] = -Hn * r[6] / muJ;
-    out[7] = -Hn * r[7] / muJ;
-    out[8] = -Hn * r[8] / muJ;
-#pragma unroll
-    for (int c = 0; c < 9; ++c) A.qb[c * F + o] += A.dt * out[c];
-  }
-}
-
-template <typename T>
-__global__ void adj_grad_kernel(const AdjArgs<T> A) {
-  const long long N = (long long)A.nq * A.nr * A.ns;
-  const std::size_t F = A.field;
-  for (long long n = blockIdx.x * (long long)blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
-    const Node nd = node_of(A, n);
-    const long long o = nd.o;
-    T ru[9], l[9];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) {
-      ru[c] = A.r[c * F + o];
-      l[c] = A.dqb[c * F + o];
-    }
-    const T J = A.jac[o];
-    const T rJ = A.coef[11 * F + o];
-    const T iJ = T(1) / J;
-    // volume terms: d(1/(rho J))/d rho = -rJ^2 J, d(lambda/J)/d lambda = d(mu/J)/d mu = 1/J
-    T g0 = -rJ * rJ * J * (l[0] * ru[0] + l[1] * ru[1] + l[2] * ru[2]);
-    const T div = T(0.5) * (ru[3] + ru[4] + ru[5]);
-    T g1 = iJ * div * (l[3] + l[4] + l[5]);
-    T g2 = iJ * (l[3] * ru[3] + l[4] * ru[4] + l[5] * ru[5] + l[6] * ru[6] + l[7] * ru[7] + l[8] * ru[8]);
-    A.grad[0 * F + o] += A.dt * g0;
-    A.grad[1 * F + o] += A.dt * g1;
-    A.grad[2 * F + o] += A.dt * g2;
-  }
-}
-
-// Face terms of one axis xi: the nodes of faces 2 xi and 2 xi + 1 (disjoint,
-// so one launch per axis has no two threads on one node).  GRAD = false:
-// Bd y + P^T dqb added to qb (times dt); GRAD = true: the derivative of the
-// penalty with respect to the node's rho, lambda, mu (dual numbers, seeded
-// with the derivatives of the face coefficients) against dqb, added to grad.
+// Face terms of one of the two faces xi at one of its nodes.  With the penalty
+// split as in face_penalty,
+//   Gn = cv Z_p v_n + ct T_n,   g = cv Z_s (v - v_n n) + ct (T - T_n n),
+// and b the vector the stress rows give to l . rate = -kr (Gn n + g) . l_v +
+// (Gn / Z_p n + g / Z_s) . b, the transpose P^T l comes from hn = -kr l_v . n +
+// b . n / Z_p (against Gn) and h = -kr l_v + b / Z_s (against g), and the
+// derivative with respect to each face coefficient is a product of the same
+// terms.  qb += dt (Bd y + P^T l); GRAD: grad += dt times the derivative with
+// respect to the node's rho, lambda, mu.
 template <typename T, bool GRAD>
-__global__ void adj_face_kernel(const AdjArgs<T> A, int xi) {
+__device__ __forceinline__ void face_node(const AdjArgs<T>& A, const Node& nd, int xi, bool side, const T l[9],
+                                          const T y[9], const T qs[9], T rho, T qb[9], T grad[3]) {
   const std::size_t F = A.field;
-  const std::size_t fn = xi == 0 ? (std::size_t)A.nr * A.ns : (xi == 1 ? (std::size_t)A.nq * A.ns
-                                                                        : (std::size_t)A.nq * A.nr);
-  const std::size_t t = blockIdx.x * (std::size_t)blockDim.x + threadIdx.x;
-  if (t >= 2 * fn) return;
-  const int side = t >= fn ? 1 : 0;
-  const int f = 2 * xi + side;
-  const std::size_t idx = t - side * fn;
-  Node nd;
-  if (xi == 0) {
-    nd.i = side ? A.nq - 1 : 0;
-    nd.j = (int)(idx % A.nr);
-    nd.k = (int)(idx / A.nr);
-  } else if (xi == 1) {
-    nd.i = (int)(idx % A.nq);
-    nd.j = side ? A.nr - 1 : 0;
-    nd.k = (int)(idx / A.nq);
-  } else {
-    nd.i = (int)(idx % A.nq);
-    nd.j = (int)(idx / A.nq);
-    nd.k = side ? A.ns - 1 : 0;
-  }
-  const long long o = A.nm(nd.i, nd.j, nd.k);
+  const std::size_t idx = xi == 0 ? (std::size_t)nd.k * A.nr + nd.j
+                                  : (xi == 1 ? (std::size_t)nd.k * A.nq + nd.i : (std::size_t)nd.j * A.nq + nd.i);
+  const std::size_t off = side ? A.face_off[2 * xi + 1] : A.face_off[2 * xi];
+  const T gamma = side ? A.gamma[2 * xi + 1] : A.gamma[2 * xi];
+  const bool traction = (side ? A.traction[2 * xi + 1] : A.traction[2 * xi]) != 0;
+  const long long o = nd.o;
   T fc[kNumFaceCoef];
 #pragma unroll
-  for (int kk = 0; kk < kNumFaceCoef; ++kk) fc[kk] = A.face[A.face_off[f] + idx + (std::size_t)kk * A.face_n[f]];
+  for (int kk = 0; kk < kNumFaceCoef; ++kk) fc[kk] = A.face[off + idx + (std::size_t)kk * A.face_n[2 * xi]];
+  const T m0 = A.coef[(3 * xi) * F + o], m1 = A.coef[(3 * xi + 1) * F + o], m2 = A.coef[(3 * xi + 2) * F + o];
   const T sgn = side ? T(1) : T(-1);
-  T l[9];
+  const T wq = norm_w(A, nd.i, A.nq), wr = norm_w(A, nd.j, A.nr), ws = norm_w(A, nd.k, A.ns);
+  // B_xi: sign times the norm weights of the two other axes
+  const T b = sgn * (xi == 0 ? A.h[1] * wr * A.h[2] * ws : (xi == 1 ? A.h[0] * wq * A.h[2] * ws : A.h[0] * wq * A.h[1] * wr));
+  T out[9];
+  // Bd y: velocity rows take the flux of y_sigma, stress rows the
+  // transposed flux map of y_v
+  out[0] = b * (m0 * y[3] + m1 * y[6] + m2 * y[7]);
+  out[1] = b * (m0 * y[6] + m1 * y[4] + m2 * y[8]);
+  out[2] = b * (m0 * y[7] + m1 * y[8] + m2 * y[5]);
+  const T z0 = b * y[0], z1 = b * y[1], z2 = b * y[2];
+  out[3] = m0 * z0;
+  out[4] = m1 * z1;
+  out[5] = m2 * z2;
+  out[6] = m1 * z0 + m0 * z1;
+  out[7] = m2 * z0 + m0 * z2;
+  out[8] = m2 * z1 + m1 * z2;
+
+  const T nx = fc[FN_X], ny = fc[FN_Y], nz = fc[FN_Z];
+  const T zp = fc[F_ZP], zs = fc[F_ZS], izp = fc[F_IZP], izs = fc[F_IZS], kr = fc[F_KR], kl = fc[F_KL], km = fc[F_KM];
+  const T ln = l[0] * nx + l[1] * ny + l[2] * nz;
+  // b = -sgn (kl tr(l_sigma) n + km s)
+  const T trl = l[3] + l[4] + l[5];
+  const T sx = T(2) * l[3] * nx + l[6] * ny + l[7] * nz, sy = l[6] * nx + T(2) * l[4] * ny + l[8] * nz,
+          sz = l[7] * nx + l[8] * ny + T(2) * l[5] * nz;
+  const T e = -sgn;
+  const T bx = e * (kl * trl * nx + km * sx), by = e * (kl * trl * ny + km * sy), bz = e * (kl * trl * nz + km * sz);
+  const T bn = bx * nx + by * ny + bz * nz;
+  const T cv = traction ? T(0) : T(0.5) * (T(1) - gamma);
+  const T ct = T(0.5) * sgn * (T(1) + gamma);
+  const T hn = izp * bn - kr * ln;
+  const T hx = izs * bx - kr * l[0], hy = izs * by - kr * l[1], hz = izs * bz - kr * l[2];
+  const T hhn = hx * nx + hy * ny + hz * nz;
+  const T gx = hx - hhn * nx, gy = hy - hhn * ny, gz = hz - hhn * nz;
+  // against the traction T = sigma n
+  const T tx = traction ? e * kr * l[0] : ct * (hn * nx + gx), ty = traction ? e * kr * l[1] : ct * (hn * ny + gy),
+          tz = traction ? e * kr * l[2] : ct * (hn * nz + gz);
+  out[0] += cv * (zp * hn * nx + zs * gx);
+  out[1] += cv * (zp * hn * ny + zs * gy);
+  out[2] += cv * (zp * hn * nz + zs * gz);
+  out[3] += tx * nx;
+  out[4] += ty * ny;
+  out[5] += tz * nz;
+  out[6] += tx * ny + ty * nx;
+  out[7] += tx * nz + tz * nx;
+  out[8] += ty * nz + tz * ny;
 #pragma unroll
-  for (int c = 0; c < 9; ++c) l[c] = A.dqb[c * F + o];
-  if constexpr (!GRAD) {
-    T y[9], out[9];
+  for (int c = 0; c < 9; ++c) qb[c] += A.dt * out[c];
+
+  if constexpr (GRAD) {
+    const T Tx = qs[3] * nx + qs[6] * ny + qs[7] * nz, Ty = qs[6] * nx + qs[4] * ny + qs[8] * nz,
+            Tz = qs[7] * nx + qs[8] * ny + qs[5] * nz;
+    const T vn = qs[0] * nx + qs[1] * ny + qs[2] * nz;
+    const T Tn = Tx * nx + Ty * ny + Tz * nz;
+    const T ux = qs[0] - vn * nx, uy = qs[1] - vn * ny, uz = qs[2] - vn * nz;
+    const T Gn = cv * zp * vn + ct * Tn;
+    const T gtx = cv * zs * ux + ct * (Tx - Tn * nx), gty = cv * zs * uy + ct * (Ty - Tn * ny),
+            gtz = cv * zs * uz + ct * (Tz - Tn * nz);
+    const T gn = Gn * izp;
+    const T Gx = gn * nx + gtx * izs, Gy = gn * ny + gty * izs, Gz = gn * nz + gtz * izs;
+    // derivatives of l . rate with respect to the face coefficients
+    const T d_kr = traction ? e * (Tx * l[0] + Ty * l[1] + Tz * l[2])
+                            : -(Gn * ln + gtx * l[0] + gty * l[1] + gtz * l[2]);
+    T d_zp = cv * vn * hn;
+    T d_zs = cv * (ux * hx + uy * hy + uz * hz);
+    T d_izp = Gn * bn;
+    T d_izs = gtx * bx + gty * by + gtz * bz;
+    T d_kl = e * trl * (nx * Gx + ny * Gy + nz * Gz);
+    T d_km = e * (sx * Gx + sy * Gy + sz * Gz);
+    if (traction) d_zp = d_zs = d_izp = d_izs = d_kl = d_km = T(0);
+    // and theirs (Z_p = sqrt(rho (lambda + 2 mu)), Z_s = sqrt(rho mu), the
+    // inverses, kappa/rho, kappa lambda, kappa mu) with respect to rho, lambda, mu
+    const T kap = kr * rho, hr = T(0.5) / rho;
+    const T zp1 = T(0.5) * rho * izp, zs2 = T(0.5) * rho * izs;
+    const T p = zp1 * (d_zp - izp * izp * d_izp);
+    grad[0] += A.dt * (hr * (zp * d_zp + zs * d_zs - izp * d_izp - izs * d_izs) - kr / rho * d_kr);
+    grad[1] += A.dt * (p + kap * d_kl);
+    grad[2] += A.dt * (T(2) * p + zs2 * (d_zs - izs * izs * d_izs) + kap * d_km);
+  }
+}
+
+// One node between two right-hand sides of the reverse sweep: -W r and the
+// face terms into qb, GRAD: the gradient terms into grad, PRE: d and y of the
+// next stage.
+template <typename T, bool GRAD, bool PRE, bool FACE>
+__device__ __forceinline__ void stage_node(const AdjArgs<T>& A, const Node& nd) {
+  const std::size_t F = A.field;
+  const long long o = nd.o;
+  T r[9], l[9], ru[9], qb[9], grad[3];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) y[c] = A.y[c * F + o];
+  for (int c = 0; c < 9; ++c) {
+    r[c] = A.r[c * F + o];
+    qb[c] = A.qb[c * F + o];
+    if constexpr (GRAD || PRE || FACE) l[c] = A.dqb[c * F + o];
+    if constexpr (GRAD) ru[c] = A.ru[c * F + o];
+  }
+  const T lamJ = A.coef[9 * F + o], muJ = A.coef[10 * F + o], rJ = A.coef[11 * F + o];
+  T J;
+  if constexpr (GRAD) {
+    J = A.jac[o];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) grad[p] = A.grad[p * F + o];
+  }
+  {
     const T wq = norm_w(A, nd.i, A.nq), wr = norm_w(A, nd.j, A.nr), ws = norm_w(A, nd.k, A.ns);
-    // B_xi: sign times the norm weights of the two other axes
-    const T bw = xi == 0 ? A.h[1] * wr * A.h[2] * ws : (xi == 1 ? A.h[0] * wq * A.h[2] * ws : A.h[0] * wq * A.h[1] * wr);
-    const T b = sgn * bw;
-    const T m0 = A.coef[(3 * xi) * F + o], m1 = A.coef[(3 * xi + 1) * F + o], m2 = A.coef[(3 * xi + 2) * F + o];
-    // Bd y: velocity rows take the flux of y_sigma, stress rows the
-    // transposed flux map of y_v
-    out[0] = b * (m0 * y[3] + m1 * y[6] + m2 * y[7]);
-    out[1] = b * (m0 * y[6] + m1 * y[4] + m2 * y[8]);
-    out[2] = b * (m0 * y[7] + m1 * y[8] + m2 * y[5]);
-    const T z0 = b * y[0], z1 = b * y[1], z2 = b * y[2];
-    out[3] = m0 * z0;
-    out[4] = m1 * z1;
-    out[5] = m2 * z2;
-    out[6] = m1 * z0 + m0 * z1;
-    out[7] = m2 * z0 + m0 * z2;
-    out[8] = m2 * z1 + m1 * z2;
-    // P^T l: column kk of the penalty block is its response to unit vector kk
-    for (int kk = 0; kk < 9; ++kk) {
-      T ev[3] = {T(0), T(0), T(0)}, es[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-      if (kk < 3) ev[kk] = T(1);
-      else es[kk - 3] = T(1);
-      T rate[9];
+    const T Hn = A.h[0] * wq * A.h[1] * wr * A.h[2] * ws;
+    T out[9];
+    // -W r: -H rho J r_v and -H J C^{-1} r_sigma
+    const T hv = -Hn / rJ, im = T(1) / muJ, hs = -Hn * im;
+    out[0] = hv * r[0];
+    out[1] = hv * r[1];
+    out[2] = hv * r[2];
+    const T trr = r[3] + r[4] + r[5];
+    const T cl = lamJ / (T(3) * lamJ + T(2) * muJ);
+    const T h2 = T(0.5) * hs;
+    out[3] = h2 * (r[3] - cl * trr);
+    out[4] = h2 * (r[4] - cl * trr);
+    out[5] = h2 * (r[5] - cl * trr);
+    out[6] = hs * r[6];
+    out[7] = hs * r[7];
+    out[8] = hs * r[8];
 #pragma unroll
-      for (int c = 0; c < 9; ++c) rate[c] = T(0);
-      face_penalty(fc, A.gamma[f], sgn, A.traction[f] != 0, ev, es, rate);
-      T s = T(0);
+    for (int c = 0; c < 9; ++c) qb[c] += A.dt * out[c];
+  }
+  if constexpr (GRAD) {
+    const T iJ = T(1) / J;
+    // volume terms: d(1/(rho J))/d rho = -rJ^2 J, d(lambda/J)/d lambda = d(mu/J)/d mu = 1/J
+    const T g0 = -rJ * rJ * J * (l[0] * ru[0] + l[1] * ru[1] + l[2] * ru[2]);
+    const T div = T(0.5) * (ru[3] + ru[4] + ru[5]);
+    const T g1 = iJ * div * (l[3] + l[4] + l[5]);
+    const T g2 = iJ * (l[3] * ru[3] + l[4] * ru[4] + l[5] * ru[5] + l[6] * ru[6] + l[7] * ru[7] + l[8] * ru[8]);
+    grad[0] += A.dt * g0;
+    grad[1] += A.dt * g1;
+    grad[2] += A.dt * g2;
+  }
+  if constexpr (FACE) {
+    T y[9], qs[9];
 #pragma unroll
-      for (int c = 0; c < 9; ++c) s += rate[c] * l[c];
-      out[kk] += s;
+    for (int c = 0; c < 9; ++c) {
+      y[c] = A.y[c * F + o];
+      if constexpr (GRAD) qs[c] = A.qs[c * F + o];
     }
+    T rho = T(0);
+    if constexpr (GRAD) rho = T(1) / (rJ * J);
+    if (nd.i == 0 || nd.i == A.nq - 1) face_node<T, GRAD>(A, nd, 0, nd.i != 0, l, y, qs, rho, qb, grad);
+    if (nd.j == 0 || nd.j == A.nr - 1) face_node<T, GRAD>(A, nd, 1, nd.j != 0, l, y, qs, rho, qb, grad);
+    if (nd.k == 0 || nd.k == A.ns - 1) face_node<T, GRAD>(A, nd, 2, nd.k != 0, l, y, qs, rho, qb, grad);
+  }
 #pragma unroll
-    for (int c = 0; c < 9; ++c) A.qb[c * F + o] += A.dt * out[c];
+  for (int c = 0; c < 9; ++c) A.qb[c * F + o] = qb[c];
+  if constexpr (GRAD) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) A.grad[p * F + o] = grad[p];
+  }
+  if constexpr (PRE) pre_node(A, nd, l, qb, lamJ, muJ, rJ);
+}
+
+// Node t of the block's surface: s faces, then the rest of the r faces, then
+// the rest of the q faces
+template <typename T>
+__device__ __forceinline__ Node face_node_of(const AdjArgs<T>& A, unsigned t) {
+  const unsigned nq = A.nq, nr = A.nr, ns = A.ns;
+  Node d;
+  if (t < 2 * nq * nr) {
+    d.i = t % nq;
+    const unsigned u = t / nq;
+    d.j = u % nr;
+    d.k = u >= nr ? ns - 1 : 0;
+  } else if ((t -= 2 * nq * nr) < 2 * nq * (ns - 2)) {
+    d.i = t % nq;
+    const unsigned u = t / nq;
+    d.k = 1 + u % (ns - 2);
+    d.j = u >= ns - 2 ? nr - 1 : 0;
   } else {
-    using D = Dual<T>;
-    D v[3], sg[6];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) v[c] = D(A.qs[c * F + o], T(0));
-#pragma unroll
-    for (int c = 0; c < 6; ++c) sg[c] = D(A.qs[(3 + c) * F + o], T(0));
-    const T rho = T(1) / (A.coef[11 * F + o] * A.jac[o]);
-    const T zp = fc[F_ZP], zs = fc[F_ZS], izp = fc[F_IZP], izs = fc[F_IZS], kr = fc[F_KR];
-    const T kap = kr * rho;
-    // derivatives of the face coefficients (Z_p = sqrt(rho (lambda + 2 mu)),
-    // Z_s = sqrt(rho mu), their inverses, kappa/rho, kappa lambda, kappa mu)
-    // with respect to rho, lambda, mu
-    T seed[3][kNumFaceCoef] = {};
-    seed[0][F_ZP] = zp / (T(2) * rho);
-    seed[0][F_ZS] = zs / (T(2) * rho);
-    seed[0][F_IZP] = -izp / (T(2) * rho);
-    seed[0][F_IZS] = -izs / (T(2) * rho);
-    seed[0][F_KR] = -kr / rho;
-    seed[1][F_ZP] = T(0.5) * rho * izp;
-    seed[1][F_IZP] = -T(0.5) * rho * izp * izp * izp;
-    seed[1][F_KL] = kap;
-    seed[2][F_ZP] = rho * izp;
-    seed[2][F_ZS] = T(0.5) * rho * izs;
-    seed[2][F_IZP] = -rho * izp * izp * izp;
-    seed[2][F_IZS] = -T(0.5) * rho * izs * izs * izs;
-    seed[2][F_KM] = kap;
-    for (int p = 0; p < 3; ++p) {
-      D dfc[kNumFaceCoef], rate[9];
-#pragma unroll
-      for (int kk = 0; kk < kNumFaceCoef; ++kk) dfc[kk] = D(fc[kk], seed[p][kk]);
-#pragma unroll
-      for (int c = 0; c < 9; ++c) rate[c] = D(T(0), T(0));
-      face_penalty(dfc, D(A.gamma[f], T(0)), D(sgn, T(0)), A.traction[f] != 0, v, sg, rate);
-      T s = T(0);
-#pragma unroll
-      for (int c = 0; c < 9; ++c) s += rate[c].d * l[c];
-      A.grad[p * F + o] += A.dt * s;
-    }
+    t -= 2 * nq * (ns - 2);
+    d.j = 1 + t % (nr - 2);
+    const unsigned u = t / (nr - 2);
+    d.k = 1 + u % (ns - 2);
+    d.i = u >= ns - 2 ? nq - 1 : 0;
+  }
+  d.o = A.nm(d.i, d.j, d.k);
+  return d;
+}
+
+// stage_node of every node: the first fb blocks take the surface (its
+// penalties are long chains on few nodes, so they start first), the rest the
+// interior.
+template <typename T, bool GRAD, bool PRE>
+__global__ __launch_bounds__(256) void adj_stage_kernel(const AdjArgs<T> A, int fb) {
+  if ((int)blockIdx.x < fb) {
+    const unsigned t = blockIdx.x * 256 + threadIdx.x;
+    if (t < surface_nodes(A)) stage_node<T, GRAD, PRE, true>(A, face_node_of(A, t));
+    return;
+  }
+  const unsigned N = (unsigned)A.nq * A.nr * A.ns;
+  for (unsigned n = (blockIdx.x - fb) * 256 + threadIdx.x; n < N; n += (gridDim.x - fb) * 256) {
+    const Node nd = node_of(A, n);
+    if (nd.i > 0 && nd.i < A.nq - 1 && nd.j > 0 && nd.j < A.nr - 1 && nd.k > 0 && nd.k < A.ns - 1)
+      stage_node<T, GRAD, PRE, false>(A, nd);
   }
 }
 
@@ -311,28 +366,17 @@ hipError_t launch_adj_pre(const AdjArgs<T>& a, hipStream_t st) {
   hipLaunchKernelGGL(adj_pre_kernel<T>, dim3(node_blocks(a)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
-template <typename T, bool GRAD>
-hipError_t launch_faces(const AdjArgs<T>& a, hipStream_t st) {
-  const std::size_t fn[3] = {(std::size_t)a.nr * a.ns, (std::size_t)a.nq * a.ns, (std::size_t)a.nq * a.nr};
-  for (int xi = 0; xi < 3; ++xi) {
-    hipLaunchKernelGGL((adj_face_kernel<T, GRAD>), dim3((unsigned)((2 * fn[xi] + 255) / 256)), dim3(256), 0, st, a,
-                       xi);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
 template <typename T>
-hipError_t launch_adj_post(const AdjArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL(adj_post_kernel<T>, dim3(node_blocks(a)), dim3(256), 0, st, a);
-  hipError_t e = hipGetLastError();
-  return e != hipSuccess ? e : launch_faces<T, false>(a, st);
-}
-template <typename T>
-hipError_t launch_adj_grad(const AdjArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL(adj_grad_kernel<T>, dim3(node_blocks(a)), dim3(256), 0, st, a);
-  hipError_t e = hipGetLastError();
-  return e != hipSuccess ? e : launch_faces<T, true>(a, st);
+hipError_t launch_adj_stage(const AdjArgs<T>& a, bool grad, bool pre, hipStream_t st) {
+  const int fb = (int)((surface_nodes(a) + 255) / 256);
+  const dim3 nb(fb + node_blocks(a)), tb(256);
+  if (!grad)
+    hipLaunchKernelGGL((adj_stage_kernel<T, false, false>), nb, tb, 0, st, a, fb);
+  else if (pre)
+    hipLaunchKernelGGL((adj_stage_kernel<T, true, true>), nb, tb, 0, st, a, fb);
+  else
+    hipLaunchKernelGGL((adj_stage_kernel<T, true, false>), nb, tb, 0, st, a, fb);
+  return hipGetLastError();
 }
 template <typename T>
 hipError_t launch_adj_inject(T* qb, std::size_t field, const long long* off, int nrec, const T* res,
@@ -351,10 +395,8 @@ hipError_t launch_fill(T* dst, std::size_t n, T v, hipStream_t st) {
 
 template hipError_t launch_adj_pre<float>(const AdjArgs<float>&, hipStream_t);
 template hipError_t launch_adj_pre<double>(const AdjArgs<double>&, hipStream_t);
-template hipError_t launch_adj_post<float>(const AdjArgs<float>&, hipStream_t);
-template hipError_t launch_adj_post<double>(const AdjArgs<double>&, hipStream_t);
-template hipError_t launch_adj_grad<float>(const AdjArgs<float>&, hipStream_t);
-template hipError_t launch_adj_grad<double>(const AdjArgs<double>&, hipStream_t);
+template hipError_t launch_adj_stage<float>(const AdjArgs<float>&, bool, bool, hipStream_t);
+template hipError_t launch_adj_stage<double>(const AdjArgs<double>&, bool, bool, hipStream_t);
 template hipError_t launch_adj_inject<float>(float*, std::size_t, const long long*, int, const float*, hipStream_t);
 template hipError_t launch_adj_inject<double>(double*, std::size_t, const long long*, int, const double*,
                                               hipStream_t);

@@ -27,8 +27,8 @@ struct AdjArgs {
   T* qb;            // adjoint state
   T* dqb;           // adjoint Runge-Kutta register
   T* y;             // W^{-1} dqb
-  const T* r;       // volume right-hand side of y (adj_post) or, with unit
-                    // material, of the forward stage input (adj_grad)
+  const T* r;       // volume right-hand side of y
+  const T* ru;      // volume right-hand side, with unit material, of qs
   const T* qs;      // forward stage input
   const T* jac;     // 1 field: J
   T* grad;          // 3 fields: d chi / d (rho, lambda, mu)
@@ -37,10 +37,11 @@ struct AdjArgs {
 
 template <typename T>
 hipError_t launch_adj_pre(const AdjArgs<T>& a, hipStream_t st);
+// what follows the right-hand sides of a reverse stage at every node: qb; grad
+// (with ru) if `grad`; then dqb and y of the next stage (factors a, b) if
+// `pre` (only with grad)
 template <typename T>
-hipError_t launch_adj_post(const AdjArgs<T>& a, hipStream_t st);
-template <typename T>
-hipError_t launch_adj_grad(const AdjArgs<T>& a, hipStream_t st);
+hipError_t launch_adj_stage(const AdjArgs<T>& a, bool grad, bool pre, hipStream_t st);
 // qb[c][off[r]] += res[r][c] for the nrec receivers (velocity components)
 template <typename T>
 hipError_t launch_adj_inject(T* qb, std::size_t field, const long long* off, int nrec, const T* res,

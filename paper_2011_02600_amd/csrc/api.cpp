@@ -949,7 +949,7 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
   bool buf_ok = true;
   for (int g = 0; g < n; ++g) {
     const StageArgs<T> a = stage_args<T>(hs[g]);
-    buf_ok = buf_ok && !a.plain && 12.0 * (double)a.field * sizeof(T) < 4294967296.0;
+    buf_ok = buf_ok && stage_buffers(a);
     buf_ok = buf_ok && worklist_order_ok<T>(hs[g]->order);
   }
   P.worklist = buf_ok && !P.tile;
@@ -1561,7 +1561,8 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
 // ---- discrete adjoint ---------------------------------------------------------
 // Layout of the caller's adjoint workspace (byte offsets): checkpoints of the
 // state every `every` steps, the state and the inputs of stages 2-5 of every
-// step of one block of steps, the stage outputs of one step, the forward
+// step of one block of steps, the stage outputs of one step (in the reverse
+// sweep the first holds the unit-material right-hand side), the forward
 // Runge-Kutta register, the adjoint state and register, W^{-1} dQb, a
 // right-hand-side buffer, the unit-material coefficients, J and the three
 // gradient fields.
@@ -1616,6 +1617,8 @@ int stage_explicit(sbp_ctx* h, const StageArgs<T>& base, int k, double dt, doubl
   if (use_tile(h)) {
     HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, b, h->stream));
   } else {
+    // (a right-hand side alone leaves no stage output: 9 of 39 words per node)
+    if (rhs_only && !sat && !sources && stage_buffers(b)) b.qout = nullptr;
     HIPCHK(launch_stage<T>(h->order, h->ty, b, h->stream));
     HIPCHK(edge_and_penalties<T>(h, b, h->stream));
   }
@@ -1696,7 +1699,7 @@ int do_adjoint_rhs(sbp_ctx* h, const void* lam, void* out, char* adj) {
   if ((rc = stage_explicit<T>(h, base, 0, 1.0, 0.0, a.y, (T*)(adj + L.st), (T*)(adj + L.r), true, base.coef, false,
                               false)))
     return rc;
-  HIPCHK(launch_adj_post<T>(a, h->stream));
+  HIPCHK(launch_adj_stage<T>(a, false, false, h->stream));
   return copy_out(h, out, adj + L.qb, 9, hipMemcpyDeviceToDevice);
 }
 
@@ -1711,12 +1714,15 @@ int adj_reverse(sbp_ctx* h, int nsteps, double dt, double t0, const T* res, cons
   if (rc) return rc;
   const StageArgs<T> base = stage_args<T>(h);
   AdjArgs<T> a = adj_args<T>(h, adj, L);
+  a.dt = (T)dt;
+  a.ru = (const T*)(adj + L.st);
   const std::size_t F9 = 9 * h->field;
   const T* ck = (const T*)(adj + L.ck);
   T* blk = (T*)(adj + L.blk);
   T* spare = (T*)(adj + L.st) + 4 * F9;
   T* dqs = (T*)(adj + L.dqs);
   T* rbuf = (T*)(adj + L.r);
+  T* ru = (T*)(adj + L.st);
   T* cu = (T*)(adj + L.cu);
   const std::size_t bytes9 = F9 * sizeof(T);
 
@@ -1745,17 +1751,16 @@ int adj_reverse(sbp_ctx* h, int nsteps, double dt, double t0, const T* res, cons
     }
     for (int n = n1 - 1; n >= n0; --n) {
       HIPCHK(launch_adj_inject<T>(a.qb, h->field, roff, h->nrec, res + (std::size_t)n * h->nrec * 3, h->stream));
+      a.a = T(0);
+      a.b = (T)kRkB[4];
+      HIPCHK(launch_adj_pre<T>(a, h->stream));
       for (int k = 4; k >= 0; --k) {
-        a.a = k == 4 ? T(0) : (T)kRkA[k + 1];
-        a.b = (T)kRkB[k];
-        a.dt = (T)dt;
-        HIPCHK(launch_adj_pre<T>(a, h->stream));
+        a.qs = slot(n) + (std::size_t)k * F9;
         if ((rc = stage_explicit<T>(h, base, 0, 1.0, 0.0, a.y, spare, rbuf, true, base.coef, false, false))) return rc;
-        HIPCHK(launch_adj_post<T>(a, h->stream));
-        const T* qs = slot(n) + (std::size_t)k * F9;
-        if ((rc = stage_explicit<T>(h, base, 0, 1.0, 0.0, qs, spare, rbuf, true, cu, false, false))) return rc;
-        a.qs = qs;
-        HIPCHK(launch_adj_grad<T>(a, h->stream));
+        if ((rc = stage_explicit<T>(h, base, 0, 1.0, 0.0, a.qs, spare, ru, true, cu, false, false))) return rc;
+        a.a = (T)kRkA[k];  // (of the next stage, k - 1)
+        a.b = k > 0 ? (T)kRkB[k - 1] : T(0);
+        HIPCHK(launch_adj_stage<T>(a, true, k > 0, h->stream));
       }
     }
   }

@@ -158,7 +158,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<T>& A, const int tile
   const std::size_t field = A.field;
   const unsigned col = (unsigned)j * px + (unsigned)i;
 
-  const Arr<T, BUF> gq(A.qin, field), gc(A.coef, field), gd(A.dq, field), go(A.qout, field);
+  const Arr<T, BUF> gq(A.qin, field), gc(A.coef, field), gd(A.dq, field), go(A.qout, field, A.qout == nullptr);
   for (int e = threadIdx.y * 64 + threadIdx.x; e < kClosureTab * TABN; e += NT) ltab[e] = A.tab[e];
   // q = 0 face coefficients of the plane, one row of kNumFaceCoef per wave
   T* const lfq = reinterpret_cast<T*>(lds) + L::o_fq;
@@ -1124,7 +1124,7 @@ __device__ __forceinline__ void edge_body(const StageArgs<T>& A, int b, char* ld
     }
     const T q0 = (c < 3) ? v[c] : sg[c - 3];
     A.dq[oc] = d;
-    A.qout[oc] = q0 + Bk * d;
+    if (A.qout) A.qout[oc] = q0 + Bk * d;
   }
 }
 
@@ -1479,8 +1479,7 @@ static hipError_t launch_stage_t(const StageArgs<T>& a, hipStream_t st) {
     return hipErrorInvalidValue;
   } else {
     const int nb = ((a.ntiles + 7) / 8) * 8;
-    // buffer addressing needs every array (at most 12 fields) below 4 GiB
-    if (!a.plain && 12.0 * (double)a.field * sizeof(T) < 4294967296.0)
+    if (stage_buffers<T>(a))
       hipLaunchKernelGGL((stage_kernel<T, ORDER, TY, true>), dim3(nb), dim3(64, TY), 0, st, a);
     else
       hipLaunchKernelGGL((stage_kernel<T, ORDER, TY, false>), dim3(nb), dim3(64, TY), 0, st, a);

@@ -35,7 +35,7 @@ struct TileShape {
 template <typename T>
 struct StageArgs {
   const T* qin;       // 9 fields, current stage input
-  T* qout;            // 9 fields, stage output
+  T* qout;            // 9 fields, stage output (null: not stored, where stage_buffers holds)
   T* dq;              // 9 fields, Runge-Kutta register (read if read_dq)
   const T* coef;      // 12 fields: M[xi][c] (3 xi + c), lambda/J, mu/J, 1/(rho J)
   const T* face;      // workspace base for the face coefficient arrays
@@ -190,6 +190,12 @@ struct RecordBatch {
   const StepClock* clock;  // non-null: slot from the clock
 };
 
+// the stage kernel's arrays through buffer resources: every array (at most 12
+// fields) below 4 GiB
+template <typename T>
+inline bool stage_buffers(const StageArgs<T>& a) {
+  return !a.plain && 12.0 * (double)a.field * sizeof(T) < 4294967296.0;
+}
 template <typename T>
 hipError_t launch_stage(int order, int ty, const StageArgs<T>& a, hipStream_t st);
 template <typename T>

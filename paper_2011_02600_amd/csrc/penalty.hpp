@@ -1,6 +1,5 @@
-// Boundary penalty of one face node (shared by the stage, edge and adjoint
-// kernels).  Written for any arithmetic type T with +, -, * and construction
-// from a constant, so that the adjoint can evaluate it on dual numbers.
+// Boundary penalty of one face node (shared by the stage, edge and tile
+// kernels; adjoint.hip holds its transpose and its derivatives).
 #pragma once
 
 #include "internal.hpp"

@@ -1,0 +1,62 @@
+"""The pass between two right-hand sides of the reverse sweep, on grids where
+its surface and interior blocks end: the transposed operator against the
+operator itself, <l, L q> = <L^T l, q> in double precision, and the gradient
+against a central difference along one direction."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+GAMMA = (0.25, -1.0, 1.0, 0.0, 0.5, -0.5)
+
+
+# smallest grids of an order (few interior nodes), surfaces and interiors below
+# and above a block of 256, grids above the tile kernel's
+@pytest.mark.parametrize("order,shape,variant,gamma", [
+    (2, (4, 4, 4), 0, GAMMA), (2, (5, 4, 6), 1, GAMMA), (4, (8, 8, 8), 1, (1.0,) * 6), (4, (8, 8, 17), 0, (1.0,) * 6),
+    (6, (12, 13, 129), 0, GAMMA), (5, (124, 122, 118), 1, (1.0, 0.0, 1.0, -1.0, 0.5, 1.0))])
+def test_transposed_operator_and_gradient(order, shape, variant, gamma):
+    from paper_2011_02600_amd import sbp
+    ns, nr, nq = shape
+    xyz = W.warped_mesh(nq, nr, ns, seed=order, amp=0.02)
+    med = W.random_medium(shape, 3)
+    s = sbp.Solver(xyz, order=order, dtype="f64", gamma=gamma, sat_variant=variant)
+    s.set_material(*med)
+    q, lam = W.random_state(shape, 1), W.random_state(shape, 2)
+    s.set_state(q, 0.0)
+    lq = s.rhs(0.0).cpu().numpy()
+    ltl = s.adjoint_rhs(torch.from_numpy(lam).cuda()).cpu().numpy()
+    a, b = (lam * lq).ravel(), (ltl * q).ravel()
+    # the transposed operator is within 4e-13 of the explicit transpose per
+    # field (test_gpu_adjoint.py): 1e-12 of the terms' sum
+    assert abs(a.sum() - b.sum()) <= 1e-12 * (np.abs(a).sum() + np.abs(b).sum())
+    if np.prod(shape) > 1e5:
+        s.close()
+        return
+    # gradient of chi = 1/2 |traces|^2 along one direction of every parameter
+    nsteps = 3
+    dt = W.cfl_dt(xyz, med[1], 0.2)
+    rec = np.array([[0, 0, ns - 1], [nq - 1, nr // 2, ns // 2], [nq // 2, nr // 2, 1]], dtype=np.int64)
+
+    def traces(r, la, m):
+        s.set_material(r, np.sqrt((la + 2 * m) / r), np.sqrt(m / r))
+        s.set_state(q, 0.0)
+        tr = s.record(rec, nsteps)
+        s.step(nsteps, dt)
+        return tr.double().cpu()
+
+    mu = med[0] * med[2] ** 2
+    base = [med[0], med[0] * med[1] ** 2 - 2 * mu, mu]
+    rng = np.random.default_rng(5)
+    dirs = [p * rng.uniform(-1, 1, size=shape) for p in base]
+    tr = traces(*base)
+    s.set_state(q, 0.0)
+    terms = s.gradient(nsteps, dt, tr, 2).cpu().numpy() * np.stack(dirs)
+    eps = 1e-5
+    chi = [0.5 * float((traces(*(p + sg * eps * d for p, d in zip(base, dirs))) ** 2).sum()) for sg in (1, -1)]
+    # central difference: eps^2 and 2^-53 / eps, both about 1e-10
+    assert abs(terms.sum() - (chi[0] - chi[1]) / (2 * eps)) <= 1e-6 * np.abs(terms).sum()
+    s.close()
