@@ -24,8 +24,8 @@
 //
 // Everything between two right-hand sides is local to a node: one launch
 // (adj_stage_kernel).  It reads and writes 73 words per node and is bound by
-// them: SP_F32 us a stage for 129^3 in single precision (the passes it replaces
-// took 256), SP_F64 for 33^3 in double (was 110), where the chain of the face
+// them: 138 us a stage for 129^3 in single precision (the nine passes it replaces
+// took 256), 26 for 33^3 in double (was 110), where the chain of the face
 // nodes counts.
 #include <hip/hip_runtime.h>
 

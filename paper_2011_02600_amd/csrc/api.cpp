@@ -124,6 +124,7 @@ struct sbp_ctx {
   // checkpoints of the last sbp_step_checkpointed (valid until the state,
   // the medium, the sources or the receivers change); ck_id names them
   bool ck_valid = false;
+  bool ck_kept = false;  // the workspace also holds the last block's stage inputs
   const char* ck_ws = nullptr;
   int ck_nsteps = 0, ck_every = 0;
   double ck_dt = 0.0, ck_t0 = 0.0;
@@ -1614,11 +1615,12 @@ int stage_explicit(sbp_ctx* h, const StageArgs<T>& base, int k, double dt, doubl
   b.sat = sat ? 1 : 0;
   const bool fused = sources && fuse_sources<T>(h, b, k, dt, tstage, rhs_only, nullptr);
   if (!sources) b.nsrc = 0;
+  const bool bare = rhs_only && !sat && !sources;
   if (use_tile(h)) {
     HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, b, h->stream));
   } else {
     // (a right-hand side alone leaves no stage output: 9 of 39 words per node)
-    if (rhs_only && !sat && !sources && stage_buffers(b)) b.qout = nullptr;
+    if (bare && stage_buffers(b)) b.qout = nullptr;
     HIPCHK(launch_stage<T>(h->order, h->ty, b, h->stream));
     HIPCHK(edge_and_penalties<T>(h, b, h->stream));
   }
@@ -1642,6 +1644,16 @@ int step_explicit(sbp_ctx* h, const StageArgs<T>& base, double tn, double dt, co
     in = out;
   }
   return SBP_OK;
+}
+
+// One step of the block of steps the reverse sweep reads: from its slot (the
+// state, then the inputs of stages 2-5) to the next slot, or to out at the
+// block's end.
+template <typename T>
+int step_keep(sbp_ctx* h, const StageArgs<T>& base, double tn, double dt, T* slot, bool more, T* out, T* dq) {
+  const std::size_t F9 = 9 * h->field;
+  T* const S[4] = {slot + F9, slot + 2 * F9, slot + 3 * F9, slot + 4 * F9};
+  return step_explicit<T>(h, base, tn, dt, slot, S, more ? slot + 5 * F9 : out, dq);
 }
 
 template <typename T>
@@ -1706,10 +1718,11 @@ int do_adjoint_rhs(sbp_ctx* h, const void* lam, void* out, char* adj) {
 // Reverse sweep of the misfit gradient over nsteps steps of size dt that
 // started at time t0, from the checkpoints in the adjoint workspace: block by
 // block from the end, each block recomputed from its checkpoint (keeping every
-// stage input of the block), then the reverse stages.
+// stage input of the block; kept: the forward run has left the last block's),
+// then the reverse stages.
 template <typename T>
 int adj_reverse(sbp_ctx* h, int nsteps, double dt, double t0, const T* res, const AdjLayout& L, char* adj,
-                void* grad_out, void* qbar_out) {
+                void* grad_out, void* qbar_out, bool kept) {
   int rc = prepare_bounds(h);
   if (rc) return rc;
   const StageArgs<T> base = stage_args<T>(h);
@@ -1743,11 +1756,10 @@ int adj_reverse(sbp_ctx* h, int nsteps, double dt, double t0, const T* res, cons
     const int n0 = c * L.every, n1 = std::min(nsteps, n0 + L.every);
     // slot n - n0 of the block: the state of step n, then its stage inputs 2-5
     auto slot = [&](int n) { return blk + (std::size_t)(n - n0) * 5 * F9; };
-    HIPCHK(hipMemcpyAsync(blk, ck + (std::size_t)c * F9, bytes9, hipMemcpyDeviceToDevice, h->stream));
-    for (int n = n0; n < n1; ++n) {
-      T* const Sn[4] = {slot(n) + F9, slot(n) + 2 * F9, slot(n) + 3 * F9, slot(n) + 4 * F9};
-      if ((rc = step_explicit<T>(h, base, t0 + n * dt, dt, slot(n), Sn, n + 1 < n1 ? slot(n + 1) : spare, dqs)))
-        return rc;
+    const bool have = kept && c == L.nck - 1;
+    if (!have) HIPCHK(hipMemcpyAsync(blk, ck + (std::size_t)c * F9, bytes9, hipMemcpyDeviceToDevice, h->stream));
+    for (int n = n0; n < n1 && !have; ++n) {
+      if ((rc = step_keep<T>(h, base, t0 + n * dt, dt, slot(n), n + 1 < n1, spare, dqs))) return rc;
     }
     for (int n = n1 - 1; n >= n0; --n) {
       HIPCHK(launch_adj_inject<T>(a.qb, h->field, roff, h->nrec, res + (std::size_t)n * h->nrec * 3, h->stream));
@@ -1792,14 +1804,21 @@ int do_gradient(sbp_ctx* h, int nsteps, double dt, const T* res, int every, char
   T* X = (T*)(adj + L.y);
   T* Y = (T*)(adj + L.r);
   HIPCHK(hipMemcpyAsync(X, state, bytes9, hipMemcpyDeviceToDevice, h->stream));
-  for (int n = 0; n < nsteps; ++n) {
+  const int nl = (L.nck - 1) * L.every;  // the last block's first step
+  for (int n = 0; n < nl; ++n) {
     if (n % L.every == 0)
       HIPCHK(hipMemcpyAsync(ck + (std::size_t)(n / L.every) * F9, X, bytes9, hipMemcpyDeviceToDevice, h->stream));
     if ((rc = step_explicit<T>(h, base, t0 + n * dt, dt, X, S, Y, dqs))) return rc;
     std::swap(X, Y);
   }
-  HIPCHK(hipMemcpyAsync(state, X, bytes9, hipMemcpyDeviceToDevice, h->stream));
-  if ((rc = adj_reverse<T>(h, nsteps, dt, t0, res, L, adj, grad_out, qbar_out))) return rc;
+  // the last block's steps, their stage inputs kept where the reverse sweep
+  // reads them
+  T* const blk = (T*)(adj + L.blk);
+  HIPCHK(hipMemcpyAsync(blk, X, bytes9, hipMemcpyDeviceToDevice, h->stream));
+  for (int n = nl; n < nsteps; ++n)
+    if ((rc = step_keep<T>(h, base, t0 + n * dt, dt, blk + (std::size_t)(n - nl) * 5 * F9, n + 1 < nsteps, state, dqs)))
+      return rc;
+  if ((rc = adj_reverse<T>(h, nsteps, dt, t0, res, L, adj, grad_out, qbar_out, true))) return rc;
   h->t = t0 + nsteps * dt;
   h->steps += nsteps;
   return SBP_OK;
@@ -1814,7 +1833,11 @@ int do_step_checkpointed(sbp_ctx* h, int nsteps, double dt, int every, char* adj
   h->ck_valid = false;
   const double t0 = h->t;
   const long long s0 = h->steps;
-  for (int n = 0; n < nsteps; ++n) {
+  // the last block's steps leave their stage inputs to the reverse sweep (not
+  // while launches are timed: those are the launches of sbp_step)
+  const bool keep = !h->prof;
+  const int nl = keep ? (L.nck - 1) * L.every : nsteps;
+  for (int n = 0; n < nl; ++n) {
     if (n % L.every == 0) {
       const T* state = (const T*)(h->ws + (h->cur ? h->off_qb : h->off_qa));
       HIPCHK(hipMemcpyAsync(adj + L.ck + (std::size_t)(n / L.every) * bytes9, state, bytes9, hipMemcpyDeviceToDevice,
@@ -1824,7 +1847,32 @@ int do_step_checkpointed(sbp_ctx* h, int nsteps, double dt, int every, char* adj
     int rc = do_steps<T>(h, 1, dt);
     if (rc) return rc;
   }
+  if (keep) {
+    int rc = prepare_bounds(h);
+    if (rc) return rc;
+    const StageArgs<T> base = stage_args<T>(h);
+    T* const blk = (T*)(adj + L.blk);
+    T* const state = (T*)(h->ws + (h->cur ? h->off_qb : h->off_qa));
+    StepClock* clk = (StepClock*)(h->ws + h->off_clock);
+    HIPCHK(hipMemcpyAsync(adj + L.ck + (std::size_t)(L.nck - 1) * bytes9, state, bytes9, hipMemcpyDeviceToDevice,
+                          h->stream));
+    HIPCHK(hipMemcpyAsync(blk, state, bytes9, hipMemcpyDeviceToDevice, h->stream));
+    if (h->nrec > 0) HIPCHK(launch_clock_set(clk, h->ws + h->off_gtab, h->rec_step, h->stream));
+    for (int n = nl; n < nsteps; ++n) {
+      T* const slot = blk + (std::size_t)(n - nl) * 5 * F9;
+      const bool more = n + 1 < nsteps;
+      if ((rc = step_keep<T>(h, base, t0 + n * dt, dt, slot, more, state, (T*)(adj + L.dqs)))) return rc;
+      if (h->nrec > 0) {
+        HIPCHK(launch_record<T>(more ? slot + 5 * F9 : state, h->field, (const long long*)(h->ws + h->off_rec), h->nrec,
+                                (T*)h->rec_out, clk, h->stream));
+        HIPCHK(launch_clock_tick(clk, h->stream));
+        ++h->rec_step;
+      }
+      ++h->steps;
+    }
+  }
   h->t = t0 + nsteps * dt;
+  h->ck_kept = keep;
   h->ck_valid = true;
   h->ck_id = ++h->ck_next;
   h->ck_ws = adj;
@@ -2244,11 +2292,14 @@ int sbp_gradient_from_checkpoints(sbp_handle h, const void* residual_device, voi
   const AdjLayout L = adj_layout(h, h->ck_nsteps, h->ck_every);
   int rc = check_adj_ws(adj_ws, adj_bytes, L.total);
   if (rc) return rc;
+  // (several blocks: the sweep ends with the first block's stage inputs there)
+  const bool kept = h->ck_kept;
+  if (L.nck > 1) h->ck_kept = false;
   return h->dtype == SBP_F32
              ? adj_reverse<float>(h, h->ck_nsteps, h->ck_dt, h->ck_t0, (const float*)residual_device, L,
-                                  (char*)adj_ws, grad_device, qbar_device)
+                                  (char*)adj_ws, grad_device, qbar_device, kept)
              : adj_reverse<double>(h, h->ck_nsteps, h->ck_dt, h->ck_t0, (const double*)residual_device, L,
-                                   (char*)adj_ws, grad_device, qbar_device);
+                                   (char*)adj_ws, grad_device, qbar_device, kept);
 }
 
 int sbp_energy(sbp_handle h, double* E) {

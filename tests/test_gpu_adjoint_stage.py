@@ -60,3 +60,43 @@ def test_transposed_operator_and_gradient(order, shape, variant, gamma):
     # central difference: eps^2 and 2^-53 / eps, both about 1e-10
     assert abs(terms.sum() - (chi[0] - chi[1]) / (2 * eps)) <= 1e-6 * np.abs(terms).sum()
     s.close()
+
+
+# one block for the whole run, a last block shorter than the others, blocks of
+# one step; grids of the tile kernel and of the march
+@pytest.mark.parametrize("order,n,dtype,nsteps,every", [
+    (4, 17, "f64", 6, 9), (4, 17, "f32", 7, 3), (3, 18, "f64", 4, 1), (6, 128, "f32", 5, 2)])
+def test_checkpointed_run_keeps_its_last_block(order, n, dtype, nsteps, every):
+    from paper_2011_02600_amd import sbp
+    shape = (n, n, n + 1)
+    xyz = W.warped_mesh(n + 1, n, n, seed=2, amp=0.02)
+    med = W.random_medium(shape, 4)
+    dt = W.cfl_dt(xyz, med[1], 0.2)
+    rec = np.array([[n, 0, 1], [n // 2, n // 2, n - 1]], dtype=np.int64)
+    s = sbp.Solver(xyz, order=order, dtype=dtype, gamma=GAMMA)
+    s.set_material(*med)
+    s.add_source((0.4, 0.6, 0.5), (1.0, 0.9, 0.8, 0.1, 0.2, 0.3), sbp.SBP_STF_RICKER, 0.3 / dt / nsteps, 2 * dt)
+    q = 0.1 * W.random_state(shape, 5, smooth=True)
+    s.set_state(q, 0.0)
+    tr = s.record(rec, 2 * nsteps)
+    s.step(nsteps, dt)
+    want = tr[:nsteps].clone()
+    s.step(nsteps, dt)
+    after, want2 = s.get_state().clone(), tr[nsteps:].clone()
+    # the checkpointed run records and ends as the plain one, also in the middle of a recording
+    s.set_state(q, 0.0)
+    tr = s.record(rec, 2 * nsteps)
+    s.step_checkpointed(nsteps, dt, every)
+    tol = 1e-12 if dtype == "f64" else 1e-5
+    res = tr[:nsteps].clone()
+    assert float((res - want).abs().max()) <= tol * float(want.abs().max())
+    g1 = s.gradient_from_checkpoints(res)
+    g2 = s.gradient_from_checkpoints(res)  # (the kept block is gone if there were several)
+    assert torch.equal(g1, g2)
+    s.step(nsteps, dt)
+    assert float((s.get_state() - after).abs().max()) <= tol * float(after.abs().max())
+    assert float((tr[nsteps:] - want2).abs().max()) <= tol * float(want2.abs().max())
+    s.set_state(q, 0.0)
+    g3 = s.gradient(nsteps, dt, res, every)
+    assert float((g3 - g1).abs().max()) <= 10 * tol * float(g1.abs().max())
+    s.close()
