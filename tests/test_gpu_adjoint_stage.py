@@ -63,7 +63,8 @@ def test_transposed_operator_and_gradient(order, shape, variant, gamma):
 
 
 # one block for the whole run, a last block shorter than the others, blocks of
-# one step; grids of the tile kernel and of the march
+# one step; grids of the tile kernel and of the march, and single-precision
+# right-hand sides on the tile kernel where the stages march (2.1 million nodes)
 @pytest.mark.parametrize("order,n,dtype,nsteps,every", [
     (4, 17, "f64", 6, 9), (4, 17, "f32", 7, 3), (3, 18, "f64", 4, 1), (6, 128, "f32", 5, 2)])
 def test_checkpointed_run_keeps_its_last_block(order, n, dtype, nsteps, every):
