@@ -1631,8 +1631,6 @@ int stage_explicit(sbp_ctx* h, const StageArgs<T>& base, int k, double dt, doubl
   if (bare ? use_tile_rhs(h) : use_tile(h)) {
     HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, b, h->stream));
   } else {
-    // (a right-hand side alone leaves no stage output: 9 of 39 words per node)
-    if (bare && stage_buffers(b)) b.qout = nullptr;
     HIPCHK(launch_stage<T>(h->order, h->ty, b, h->stream));
     HIPCHK(edge_and_penalties<T>(h, b, h->stream));
   }

@@ -158,7 +158,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<T>& A, const int tile
   const std::size_t field = A.field;
   const unsigned col = (unsigned)j * px + (unsigned)i;
 
-  const Arr<T, BUF> gq(A.qin, field), gc(A.coef, field), gd(A.dq, field), go(A.qout, field, A.qout == nullptr);
+  const Arr<T, BUF> gq(A.qin, field), gc(A.coef, field), gd(A.dq, field), go(A.qout, field);
   for (int e = threadIdx.y * 64 + threadIdx.x; e < kClosureTab * TABN; e += NT) ltab[e] = A.tab[e];
   // q = 0 face coefficients of the plane, one row of kNumFaceCoef per wave
   T* const lfq = reinterpret_cast<T*>(lds) + L::o_fq;
@@ -1124,7 +1124,7 @@ __device__ __forceinline__ void edge_body(const StageArgs<T>& A, int b, char* ld
     }
     const T q0 = (c < 3) ? v[c] : sg[c - 3];
     A.dq[oc] = d;
-    if (A.qout) A.qout[oc] = q0 + Bk * d;
+    A.qout[oc] = q0 + Bk * d;
   }
 }
 

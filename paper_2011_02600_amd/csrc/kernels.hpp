@@ -35,7 +35,7 @@ struct TileShape {
 template <typename T>
 struct StageArgs {
   const T* qin;       // 9 fields, current stage input
-  T* qout;            // 9 fields, stage output (null: not stored, where stage_buffers holds)
+  T* qout;            // 9 fields, stage output
   T* dq;              // 9 fields, Runge-Kutta register (read if read_dq)
   const T* coef;      // 12 fields: M[xi][c] (3 xi + c), lambda/J, mu/J, 1/(rho J)
   const T* face;      // workspace base for the face coefficient arrays

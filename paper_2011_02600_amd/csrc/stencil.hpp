@@ -79,9 +79,8 @@ template <typename T>
 struct Arr<T, true> {
   __amdgpu_buffer_rsrc_t r;
   unsigned fbytes;
-  // none: every access is out of the resource's range, stores go nowhere
-  __device__ Arr(const T* p, std::size_t field, bool none = false)
-      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), (short)0, none ? 0 : -1, 0x00020000)),
+  __device__ Arr(const T* p, std::size_t field)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), (short)0, -1, 0x00020000)),
         fbytes((unsigned)(field * sizeof(T))) {}
   static constexpr int kNT = 2;  // cache policy: non-temporal
   template <int POL = 0>
@@ -110,7 +109,7 @@ template <typename T>
 struct Arr<T, false> {
   T* p;
   std::size_t field;
-  __device__ Arr(const T* p_, std::size_t f, bool = false) : p(const_cast<T*>(p_)), field(f) {}
+  __device__ Arr(const T* p_, std::size_t f) : p(const_cast<T*>(p_)), field(f) {}
   __device__ __forceinline__ T ld(int c, unsigned off) const { return ldf(p + c * field, off); }
   __device__ __forceinline__ T ldn(int c, unsigned off) const { return ldf(p + c * field, off); }
   __device__ __forceinline__ void st(int c, unsigned off, T v) const { stf(p + c * field, off, v); }
