@@ -700,7 +700,7 @@ int run_stage(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, bool
 }
 
 // The launches of one step on stream st, the state starting in buffer
-// parity c (0: Q_a): five stages, the receivers, the clock tick.  Every step
+// parity c (0: Q_a): five stages, the receivers and the clock tick.  Every step
 // issues the same launches; the step-dependent values (source-time factors,
 // receiver slot) come from the clock.
 template <typename T>
@@ -716,7 +716,8 @@ int step_launches(sbp_ctx* h, StageArgs<T>& a, int c, double dt, hipStream_t st)
   if (h->nrec > 0)
     HIPCHK(launch_record<T>(c ? qb : qa, h->field, (const long long*)(h->ws + h->off_rec), h->nrec, (T*)h->rec_out,
                             clk, st));
-  HIPCHK(launch_clock_tick(clk, st));
+  else if (!h->src.empty())  // (nothing else reads the clock)
+    HIPCHK(launch_clock_tick(clk, st));
   return SBP_OK;
 }
 
@@ -1875,7 +1876,6 @@ int do_step_checkpointed(sbp_ctx* h, int nsteps, double dt, int every, char* adj
       if (h->nrec > 0) {
         HIPCHK(launch_record<T>(more ? slot + 5 * F9 : state, h->field, (const long long*)(h->ws + h->off_rec), h->nrec,
                                 (T*)h->rec_out, clk, h->stream));
-        HIPCHK(launch_clock_tick(clk, h->stream));
         ++h->rec_step;
       }
       ++h->steps;

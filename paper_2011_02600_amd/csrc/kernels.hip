@@ -1412,16 +1412,21 @@ __global__ void record_kernel_batch(const RecordBatch<T> B) {
 }
 
 // receivers: out[(slot * nrec + r) * 3 + c] = v_c(node_r), slot = the clock's
-// receiver slot of the current step (or 0 without a clock: out is the slot)
+// receiver slot of the current step.
+// tick (one block): the step's last launch also counts it.
 template <typename T>
 __global__ void record_kernel(const T* __restrict__ q, std::size_t field, const long long* __restrict__ off,
-                              int nrec, T* __restrict__ out, const StepClock* __restrict__ clock) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrec) return;
-  const long long o = off[r];
-  const std::size_t slot = clock ? (std::size_t)(clock->rec0 + clock->step) : 0;
+                              int nrec, T* __restrict__ out, StepClock* clock, int tick) {
+  const std::size_t slot = (std::size_t)(clock->rec0 + clock->step);
+  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nrec; r += gridDim.x * blockDim.x) {
+    const long long o = off[r];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) out[(slot * nrec + r) * 3 + c] = q[c * field + o];
+    for (int c = 0; c < 3; ++c) out[(slot * nrec + r) * 3 + c] = q[c * field + o];
+  }
+  if (tick) {
+    __syncthreads();
+    if (threadIdx.x == 0) clock->step += 1;
+  }
 }
 
 __global__ void clock_set_kernel(StepClock* c, const void* gtab, long long rec0) {
@@ -1768,10 +1773,19 @@ hipError_t launch_source(const SourceArgs<T>& s, int nsrc, hipStream_t st) {
 }
 
 template <typename T>
-hipError_t launch_record(const T* q, std::size_t field, const long long* off, int nrec, T* out,
-                         const StepClock* clock, hipStream_t st) {
-  hipLaunchKernelGGL(record_kernel<T>, dim3((nrec + 255) / 256), dim3(256), 0, st, q, field, off, nrec, out, clock);
-  return hipGetLastError();
+hipError_t launch_record(const T* q, std::size_t field, const long long* off, int nrec, T* out, StepClock* clock,
+                         hipStream_t st) {
+  // up to 4096 receivers in one block that ticks the clock as well: a launch of
+  // its own for the tick is 4.9 us of every step, four rounds of one block cost
+  // less
+  if (nrec <= 4096) {
+    hipLaunchKernelGGL(record_kernel<T>, dim3(1), dim3(nrec <= 256 ? 256 : 1024), 0, st, q, field, off, nrec, out,
+                       clock, 1);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(record_kernel<T>, dim3((nrec + 255) / 256), dim3(256), 0, st, q, field, off, nrec, out, clock, 0);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_clock_tick(clock, st);
 }
 
 hipError_t launch_clock_set(StepClock* c, const void* gtab, long long rec0, hipStream_t st) {
@@ -1821,9 +1835,9 @@ template hipError_t launch_penalty_batch<double>(const BatchArgs<double>&, hipSt
 template hipError_t launch_source<float>(const SourceArgs<float>&, int, hipStream_t);
 template hipError_t launch_source<double>(const SourceArgs<double>&, int, hipStream_t);
 template hipError_t launch_record<float>(const float*, std::size_t, const long long*, int, float*,
-                                         const StepClock*, hipStream_t);
+                                         StepClock*, hipStream_t);
 template hipError_t launch_record<double>(const double*, std::size_t, const long long*, int, double*,
-                                          const StepClock*, hipStream_t);
+                                          StepClock*, hipStream_t);
 template hipError_t launch_energy<float>(const EnergyArgs<float>&, int, hipStream_t);
 template hipError_t launch_energy<double>(const EnergyArgs<double>&, int, hipStream_t);
 

@@ -257,9 +257,10 @@ __host__ __device__ inline long long surface_nodes(int nq, int nr, int ns, bool 
 }
 template <typename T>
 hipError_t launch_source(const SourceArgs<T>& s, int nsrc, hipStream_t st);
+// the receivers of the step the clock is at; then the clock ticks
 template <typename T>
-hipError_t launch_record(const T* q, std::size_t field, const long long* off, int nrec, T* out,
-                         const StepClock* clock, hipStream_t st);
+hipError_t launch_record(const T* q, std::size_t field, const long long* off, int nrec, T* out, StepClock* clock,
+                         hipStream_t st);
 hipError_t launch_clock_set(StepClock* c, const void* gtab, long long rec0, hipStream_t st);
 hipError_t launch_clock_tick(StepClock* c, hipStream_t st);
 template <typename T>
