@@ -301,8 +301,8 @@ int sbp_adjoint_rhs(sbp_handle h, const void* lam_device, void* out_device, void
  * data|^2 the residual is traces - data).  Starting from the current state
  * at the current time, runs nsteps steps of size dt (sources included,
  * receiver traces not recorded), keeping a checkpoint every `every` steps in
- * adj_ws, then the reverse sweep: each block of steps is recomputed from
- * its checkpoint, keeping the inputs of every stage of the block.  Writes d chi /
+ * adj_ws, then the reverse sweep: each block of steps but the last, which
+ * the forward run has kept, is recomputed from its checkpoint, keeping the inputs of every stage of the block.  Writes d chi /
  * d (rho, lambda, mu) at every node to grad_device (3 dense grid functions:
  * rho, then lambda, then mu, with the other two held fixed) and, if
  * qbar_device is not NULL, d chi / d Q0 (9 dense grid functions).  The
