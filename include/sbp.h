@@ -396,9 +396,11 @@ int sbp_profile(sbp_handle h, double* stage_ms, double* edge_ms, long long* nsta
  * Launch-shape autotuner.  Times `reps` right-hand-side evaluations of the
  * handle's own grid for each candidate launch shape (tile height 8, and 16
  * for SBP_F32 at orders up to 7; the cost model's number of s-chunks and one
- * fewer / one more) and keeps the fastest, as sbp_set_launch would -- or the
- * tile kernel, where that is the automatic choice (see sbp_set_launch) and
- * faster than every shape.  Writes the tile height and s-chunk length of the
+ * fewer / one more) and keeps the fastest in place of a shape set before -- or
+ * the tile kernel, where that is the automatic choice (see sbp_set_launch) and
+ * faster than every shape.  Above 1.75 million nodes, where it times the stage
+ * kernel alone, the reverse sweep's right-hand sides keep their automatic
+ * choice.  Writes the tile height and s-chunk length of the
  * fastest shape and the time per evaluation (ms) of what it keeps to the
  * outputs (each may be NULL).  The state and time are not changed; call
  * it between steps.  Synchronises the stream.

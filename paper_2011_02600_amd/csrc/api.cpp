@@ -114,7 +114,8 @@ struct sbp_ctx {
   int nxt = 0, nyt = 0, nzc = 0;
   int ex = 0, ey = 0;   // last q column / last r row computed by the edge kernel
   bool bounds_dirty = true;
-  bool shape_set = false;  // launch shape ty, zchunk of the caller's (sbp_set_launch, sbp_autotune)
+  bool shape_set = false;    // launch shape ty, zchunk of the caller's (sbp_set_launch)
+  bool shape_tuned = false;  // and of sbp_autotune's, where the tile kernel was not the faster or not timed
   TileShape tile{};        // tile kernel's launch shape
   // launch timing (sbp_set_profiling)
   bool prof = false;
@@ -504,7 +505,7 @@ int prepare_bounds(sbp_ctx* h) {
 constexpr std::size_t kTileNodes = 1750000;
 
 bool use_tile(const sbp_ctx* h) {
-  return !h->shape_set && !h->plain && h->g.n <= kTileNodes;
+  return !h->shape_set && !h->shape_tuned && !h->plain && h->g.n <= kTileNodes;
 }
 
 // The same for a right-hand side alone without penalties (the reverse sweep's).
@@ -512,11 +513,14 @@ bool use_tile(const sbp_ctx* h) {
 // nothing from: in single precision the tile kernel stays ahead up to 4.5
 // million nodes (order 6, tile and march with its edge launch: 2.15e6 nodes 119
 // and 136 us, 4.17e6 nodes 43 us less, 7.19e6 13 us more; order 8 equal); in
-// double precision they take turns above kTileNodes.
+// double precision they take turns above kTileNodes.  sbp_autotune's shape does
+// not count above kTileNodes: it is the fastest of the march's, and the tile
+// kernel was not among what it timed.
 constexpr std::size_t kTileRhsNodes = 4500000;
 
 bool use_tile_rhs(const sbp_ctx* h) {
-  return use_tile(h) || (h->dtype == SBP_F32 && !h->shape_set && !h->plain && h->g.n <= kTileRhsNodes);
+  return use_tile(h) || (h->dtype == SBP_F32 && !h->shape_set && !h->plain && h->g.n > kTileNodes &&
+                         h->g.n <= kTileRhsNodes);
 }
 
 double stf_value(const Src& s, double t) {
@@ -1511,7 +1515,7 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
   std::vector<int> tys{8};
   if (sizeof(T) == 4 && h->order <= 7) tys.push_back(16);  // 16-row order-8 tiles exceed the LDS
   const std::vector<Src> saved = h->src;
-  const bool was_set = h->shape_set;
+  const bool was_set = h->shape_set, was_tuned = h->shape_tuned;
   h->src.clear();
   hipEvent_t e0 = nullptr, e1 = nullptr;
   HIPCHK(hipEventCreate(&e0));
@@ -1541,9 +1545,9 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
   };
   // the automatic choice, where that is the tile kernel
   double tile_ms = -1.0;
-  h->shape_set = false;
+  h->shape_set = h->shape_tuned = false;
   if (use_tile(h)) rc = time_rhs(&tile_ms);
-  h->shape_set = true;
+  h->shape_tuned = true;
   for (int ty : tys) {
     if (rc) break;
     if (ty < h->cl.m) continue;
@@ -1575,10 +1579,11 @@ int do_autotune(sbp_ctx* h, int reps, int* best_ty, int* best_zchunk, double* be
   h->bounds_dirty = true;
   if (rc) {
     h->shape_set = was_set;
+    h->shape_tuned = was_tuned;
     return rc;
   }
   if (tile_ms >= 0 && (best < 0 || tile_ms <= best)) {
-    h->shape_set = false;
+    h->shape_tuned = false;
     best = tile_ms;
   }
   if (best_ty) *best_ty = bty;

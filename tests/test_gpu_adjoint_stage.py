@@ -101,3 +101,26 @@ def test_checkpointed_run_keeps_its_last_block(order, n, dtype, nsteps, every):
     g3 = s.gradient(nsteps, dt, res, every)
     assert float((g3 - g1).abs().max()) <= 10 * tol * float(g1.abs().max())
     s.close()
+
+
+def test_autotune_leaves_the_reverse_sweeps_kernel():
+    """Above 1.75 million nodes sbp_autotune times the march's shapes alone, so
+    its choice does not take the penalty-free right-hand sides off the tile
+    kernel: the transposed operator keeps its bits.  A shape of the caller's
+    does select the march, which rounds differently."""
+    from paper_2011_02600_amd import sbp
+    shape = (121, 121, 122)
+    s = sbp.Solver(W.unit_cube(122, 121, 121), order=4, dtype="f32", gamma=GAMMA)
+    s.set_material(*W.random_medium(shape, 4))
+    lam = torch.from_numpy(W.random_state(shape, 6, smooth=True)).cuda()
+    want = s.adjoint_rhs(lam).clone()
+    s.autotune(1)
+    assert torch.equal(s.adjoint_rhs(lam), want)
+    s.set_launch(8, 0)
+    march = s.adjoint_rhs(lam)
+    assert not torch.equal(march, want)
+    # single precision, sums of some 60 terms in another order
+    assert float((march - want).abs().max()) <= 1e-5 * float(want.abs().max())
+    s.autotune(1)
+    assert torch.equal(s.adjoint_rhs(lam), want)
+    s.close()
