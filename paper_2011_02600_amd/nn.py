@@ -226,6 +226,10 @@ class SpectralOperator:
         """x: (S, n, n, n) float32 device tensor -> (S, R, T) traces."""
         S, C, P, L = x.shape[0], self.C, self.P, self.L
         p, st, lb = self.params, self.stream, lib()
+        if not x.is_contiguous():  # (every call reads x as dense; copied on the stream that reads it)
+            cuda = self.torch.cuda
+            with cuda.stream(cuda.ExternalStream(st, self.dev) if st else cuda.default_stream(self.dev)):
+                x = x.contiguous()
         self.S = S
         self.x = x
         self.was_fused = self._fits(S)
@@ -266,9 +270,8 @@ class SpectralOperator:
 
     def _fits(self, S):
         """Whether a batch of S media takes the fused layers: their shape, the
-        batch limit of the calls they replace, contiguous 16-byte rows of x."""
-        return self.fused and S > 0 and S * self.C * self.n <= 65535 and self.x.is_contiguous() \
-            and self.x.data_ptr() % 16 == 0
+        batch limit of the calls they replace, 16-byte rows of x."""
+        return self.fused and S > 0 and S * self.C * self.n <= 65535 and self.x.data_ptr() % 16 == 0
 
     def _forward_fused(self, x):
         """The layers as fused passes over the activations; returns the last

@@ -57,3 +57,37 @@ def test_layers_outside_the_fused_shapes_take_the_separate_calls():
     x = torch.ones((1, 16, 16, 17), device="cuda")[..., 1:]  # rows that are not 16-byte aligned
     net.forward(x.contiguous())
     assert net.was_fused
+
+
+# a grid of the fused layers and one of the separate calls
+@pytest.mark.parametrize("n", [16, 18])
+def test_strided_and_misaligned_inputs(n):
+    """A strided view of the media gives what its dense copy gives, forward and
+    backward; a dense view off the 16-byte grid takes the separate calls."""
+    import torch
+    from paper_2011_02600_amd import nn
+    rng = np.random.default_rng(n)
+    pos, T, S = [3, n ** 3 - 2, n * n], 20, 2
+    ref = torch.tensor(rng.standard_normal((S, len(pos), T)).astype(np.float32), device="cuda")
+    wide = torch.tensor(rng.standard_normal((S, n, n, n + 1)).astype(np.float32), device="cuda")
+    flat = torch.zeros(S * n ** 3 + 1, device="cuda")
+    off = flat[1:].view(S, n, n, n)
+    views = {"dense": wide[..., 1:].contiguous(), "strided": wide[..., 1:],
+             "transposed": wide[..., 1:].transpose(1, 3).contiguous().transpose(1, 3), "offset": off}
+    off.copy_(views["dense"])
+    want = {}
+    for name, x in views.items():
+        net = nn.SpectralOperator(n, 4, 8, 2, pos, T, seed=1)
+        y = net.forward(x)
+        _, dy = net.loss(y, ref, 0.5)
+        net.backward(dy)
+        assert net.was_fused == (n == 16 and name != "offset"), name
+        got = dict(net.grads, y=y)
+        if name == "dense":
+            want = {k: v.clone() for k, v in got.items()}
+        for k, v in got.items():
+            if name == "offset" and n == 16 and k not in ("y", "D", "b_out") and k[0] != "R":
+                # the separate calls sum over the grid in another order
+                assert (v - want[k]).double().norm() <= 1e-5 * want[k].double().norm(), (name, k)
+            else:
+                assert torch.equal(v, want[k]), (name, k)
