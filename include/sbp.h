@@ -244,6 +244,8 @@ int sbp_set_graphs(sbp_handle h, int on);
  * same dtype and the same stream, distinct handles and a medium; the argument
  * tables and the work list (at most 65536 items) live in the workspace of the
  * first handle of each group.  Synchronises the stream before returning.
+ * A refused call (SBP_EINVAL, SBP_ESTATE) has advanced no handle; after
+ * SBP_EHIP some may have done their steps (sbp_time).
  */
 int sbp_step_batch(sbp_handle* hs, int n, int nsteps, const double* dt);
 

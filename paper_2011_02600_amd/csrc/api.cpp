@@ -1333,10 +1333,12 @@ bool batch_groups(sbp_ctx* const* hs, int n) {
 }
 
 // A batch's grids are independent, so it runs in groups, each all its steps
-// before the next group's: grids the tile kernel serves in groups of at most
-// kGroupBytes of fields (39 per node and value), so that a group's fields stay
-// in the 256 MB memory-side cache from stage to stage; all larger grids
-// together over the work list (a single one as sbp_step would).
+// before the next group's: all larger grids together over the work list (a
+// single one as sbp_step would); grids the tile kernel serves in groups of at
+// most kGroupBytes of fields (39 per node and value), so that a group's fields
+// stay in the 256 MB memory-side cache from stage to stage.  The larger grids
+// go first: only their work list can turn out too long, and a batch that is
+// refused has then advanced no handle.
 // us per stage of 16 shots of 64^3, order 4, with the work list and in groups
 // of 1, 2, 3, 4, 6, 8 and 16: single precision 289, and 355, 286, 258, 233,
 // 258, 294, 288; double 562, and 570, 476, 469, 538, 532, 520, 507.  Eight
@@ -1367,22 +1369,19 @@ int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
     nodes = 0;
     return rc;
   };
-  for (int g : small) {
-    if (!gh.empty() && nodes + hs[g]->g.n > cap) {
-      const int rc = run(true);
-      if (rc) return rc;
-    }
-    gh.push_back(hs[g]);
-    gd.push_back(dt[g]);
-    nodes += hs[g]->g.n;
-  }
-  int rc = run(true);
-  if (rc) return rc;
   for (int g : large) {
     gh.push_back(hs[g]);
     gd.push_back(dt[g]);
   }
-  return run(false);
+  int rc = run(false);
+  for (int g : small) {
+    if (rc) return rc;
+    if (!gh.empty() && nodes + hs[g]->g.n > cap) rc = run(true);
+    gh.push_back(hs[g]);
+    gd.push_back(dt[g]);
+    nodes += hs[g]->g.n;
+  }
+  return rc ? rc : run(true);
 }
 
 // Batch launch-shape autotuner: times `reps` right-hand-side evaluations of

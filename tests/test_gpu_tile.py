@@ -111,3 +111,25 @@ def test_batch_of_small_and_large_grids(dtype):
         assert e <= tol and t <= tol and a.time() == b.time()
     for s in alone + together:
         s.close()
+
+
+def test_refused_batch_advances_no_handle():
+    """Two grids whose stage tiles exceed the work list (4 x 8 x 4 of a tile's
+    nodes used) beside small grids that hold half of the nodes: the batch is
+    refused, and no handle of it has moved."""
+    from paper_2011_02600_amd import sbp
+    print("case: refused batch", flush=True)
+    grids = [(4, 262144, 4)] * 2 + [(121, 119, 118)] * 5  # (nq, nr, ns)
+    assert 2 * 5 * 121 * 119 * 118 >= sum(a * b * c for a, b, c in grids)
+    ss = []
+    for nq, nr, ns in grids:
+        s = sbp.Solver(W.unit_cube(nq, nr, ns), order=2, dtype="f32")
+        s.set_material(2.7, 6.0, 3.464)
+        ss.append(s)
+        print("  handle", len(ss), flush=True)
+    with pytest.raises(sbp.SBPError) as e:
+        sbp.sbp_step_batch([s.h for s in ss], 2, [1e-6] * len(ss))
+    assert e.value.code == sbp.SBP_EINVAL and "blocks of work" in str(e.value)
+    for s in ss:
+        assert s.time() == (0.0, 0)
+        s.close()
