@@ -218,8 +218,8 @@ int sbp_set_graphs(sbp_handle h, int on);
  * dt[i] (host array of n doubles): batched stepping of many independent
  * sources or media ("shots") on grids of uneven size and mixed interior
  * orders.
- * Handles of up to 1.75 million nodes (without plain addressing) run in
- * groups small enough for a group's fields to stay in the memory-side cache,
+ * Handles of up to 1.75 million nodes (without plain addressing or a launch
+ * shape of the caller's, sbp_set_launch) run in groups small enough for a group's fields to stay in the memory-side cache,
  * one group's steps after the other's; per stage and interior order of a
  * group one launch of the tile kernel covers all its grids, penalties and
  * sources included.  The larger handles run together: per stage one launch

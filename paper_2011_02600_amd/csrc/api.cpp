@@ -1315,9 +1315,9 @@ int do_steps_group(sbp_ctx** hs, int n, int nsteps, const double* dt, bool tile)
   return SBP_OK;
 }
 
-// whether a grid of a batch runs in a tile-kernel group (as use_tile; a
-// batch does not use the handles' own launch shapes)
-bool batch_tile(const sbp_ctx* h) { return !h->plain && h->g.n <= kTileNodes; }
+// whether a grid of a batch runs in a tile-kernel group: as use_tile, but a
+// shape that sbp_autotune chose for the grid alone does not count
+bool batch_tile(const sbp_ctx* h) { return !h->shape_set && !h->plain && h->g.n <= kTileNodes; }
 // Whether such grids leave the work list: they do if they are at least half of
 // the batch's nodes.  A few small grids beside large ones fill the list's gaps
 // instead (32 cubes of 65 to 193 points, 8 % of the nodes in small ones: all
