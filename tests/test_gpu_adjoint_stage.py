@@ -124,3 +124,40 @@ def test_autotune_leaves_the_reverse_sweeps_kernel():
     s.autotune(1)
     assert torch.equal(s.adjoint_rhs(lam), want)
     s.close()
+
+
+# single precision on the march (a caller's launch shape): tiles with edge
+# blocks, an order without work-list kernels
+@pytest.mark.parametrize("order,shape,variant", [(4, (11, 17, 65), 0), (6, (13, 12, 40), 1), (3, (9, 25, 70), 1),
+                                                 (8, (16, 17, 65), 0)])
+def test_single_precision_reverse_sweep_on_the_march(order, shape, variant):
+    from oracle import adjoint as ADJ
+    from oracle import elastic as E
+    from paper_2011_02600_amd import sbp
+    ns, nr, nq = shape
+    xyz = W.warped_mesh(nq, nr, ns, seed=order + nq, amp=0.02)
+    med = W.random_medium(shape, 7)
+    lam = W.random_state(shape, 9, smooth=True)
+    q, nsteps = 0.1 * W.random_state(shape, 5, smooth=True), 6
+    dt = W.cfl_dt(xyz, med[1], 0.2)
+    rec = np.array([[nq - 1, 0, 1], [nq // 2, nr // 2, ns - 1]], dtype=np.int64)
+    want = ADJ.adjoint_rhs(E.Block(xyz, order).set_material(*med), lam, GAMMA, variant)
+    rhs, grads = {}, {}
+    for name, dtype in (("march", "f32"), ("tile", "f32"), ("double", "f64")):
+        s = sbp.Solver(xyz, order=order, dtype=dtype, gamma=GAMMA, sat_variant=variant)
+        s.set_material(*med)
+        if name == "march":
+            s.set_launch(8, 0)
+        rhs[name] = s.adjoint_rhs(torch.from_numpy(lam).cuda()).double().cpu().numpy()
+        s.set_state(q, 0.0)
+        tr = s.record(rec, nsteps)
+        s.step_checkpointed(nsteps, dt, 4)
+        if name == "march":
+            res = tr.clone()
+        grads[name] = s.gradient_from_checkpoints(res.to(tr.dtype)).double().cpu().numpy()
+        s.close()
+    assert not np.array_equal(rhs["march"], rhs["tile"])  # (another kernel)
+    # the bars of test_gpu_adjoint.py
+    for got, ref, tol in ((rhs["march"], want, 1e-5), (grads["march"], grads["double"], 1e-4)):
+        for g, w in zip(got, ref):
+            assert np.abs(g - w).max() <= tol * np.abs(w).max()
