@@ -17,6 +17,7 @@
 #include "adjoint.hpp"
 #include "host_math.hpp"
 #include "kernels.hpp"
+#include "route.hpp"
 #include "tile.hpp"
 
 using namespace sbp;
@@ -522,6 +523,10 @@ bool use_tile_rhs(const sbp_ctx* h) {
   return use_tile(h) || (h->dtype == SBP_F32 && !h->shape_set && !h->plain && h->g.n > kTileNodes &&
                          h->g.n <= kTileRhsNodes);
 }
+
+// bytes of a grid's fields: two states, the Runge-Kutta register and the
+// coefficients, whose rows of nq - 1 nodes are padded to 128 bytes
+double field_bytes(const sbp_ctx* h) { return (27.0 + kNumCoef) * (double)h->field * h->esize; }
 
 double stf_value(const Src& s, double t) {
   if (s.stf == SBP_STF_RICKER) {
@@ -1334,27 +1339,19 @@ bool batch_groups(sbp_ctx* const* hs, int n) {
 
 // A batch's grids are independent, so it runs in groups, each all its steps
 // before the next group's: all larger grids together over the work list (a
-// single one as sbp_step would); grids the tile kernel serves in groups of at
-// most kGroupBytes of fields (39 per node and value), so that a group's fields
-// stay in the 256 MB memory-side cache from stage to stage.  The larger grids
-// go first: only their work list can turn out too long, and a batch that is
-// refused has then advanced no handle.
-// us per stage of 16 shots of 64^3, order 4, with the work list and in groups
-// of 1, 2, 3, 4, 6, 8 and 16: single precision 289, and 355, 286, 258, 233,
-// 258, 294, 288; double 562, and 570, 476, 469, 538, 532, 520, 507.  Eight
-// cubes of 65 to 129 points: 632 and 577; 16 of 33^3: 103 and 37.
-constexpr double kGroupBytes = 200e6;
-
+// single one as sbp_step would), grids the tile kernel serves in groups that
+// fit the memory-side cache (tile_groups).  The larger grids go first: only
+// their work list can turn out too long, and a batch that is refused has then
+// advanced no handle.  us per stage, work list and groups: eight cubes of 65 to
+// 129 points 632 and 577, 16 of 33^3 103 and 37.
 template <typename T>
 int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
-  const std::size_t cap = (std::size_t)(kGroupBytes / (39.0 * sizeof(T)));
   std::vector<int> small, large;
   const bool groups = batch_groups(hs, n);
   for (int g = 0; g < n; ++g) (groups && batch_tile(hs[g]) ? small : large).push_back(g);
   std::stable_sort(small.begin(), small.end(), [&](int a, int b) { return hs[a]->g.n < hs[b]->g.n; });
   std::vector<sbp_ctx*> gh;
   std::vector<double> gd;
-  std::size_t nodes = 0;
   auto run = [&](bool tile) -> int {
     int rc = SBP_OK;
     if (gh.empty()) return rc;
@@ -1366,22 +1363,23 @@ int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
     }
     gh.clear();
     gd.clear();
-    nodes = 0;
     return rc;
   };
-  for (int g : large) {
+  auto add = [&](int g) {
     gh.push_back(hs[g]);
     gd.push_back(dt[g]);
-  }
+  };
+  for (int g : large) add(g);
   int rc = run(false);
-  for (int g : small) {
-    if (rc) return rc;
-    if (!gh.empty() && nodes + hs[g]->g.n > cap) rc = run(true);
-    gh.push_back(hs[g]);
-    gd.push_back(dt[g]);
-    nodes += hs[g]->g.n;
+  std::vector<double> bytes;
+  for (int g : small) bytes.push_back(field_bytes(hs[g]));
+  int i = 0;
+  for (int end : tile_groups(bytes)) {
+    if (rc) break;
+    for (; i < end; ++i) add(small[i]);
+    rc = run(true);
   }
-  return rc ? rc : run(true);
+  return rc;
 }
 
 // Batch launch-shape autotuner: times `reps` right-hand-side evaluations of
