@@ -358,8 +358,9 @@ int sbp_energy(sbp_handle h, double* E);
  * (8 or 16; 16 only for SBP_F32 at orders 2 to 7, else SBP_EINVAL) and
  * zchunk planes per block along s (>= 1; 0 = automatic).  Without this call
  * a handle of up to 1.75 million nodes runs a stage as one launch of the
- * tile kernel, which has no launch shape; with it the stage kernel runs, with
- * the shape given.
+ * tile kernel, which has no launch shape (in SBP_F32 unless an estimate from
+ * its shape and order favours the stage kernel); with it the stage kernel
+ * runs, with the shape given.
  * Does not change results beyond floating-point summation order (it does
  * not change it at all: every node is computed by the same instructions).
  */
@@ -400,9 +401,8 @@ int sbp_profile(sbp_handle h, double* stage_ms, double* edge_ms, long long* nsta
  * for SBP_F32 at orders up to 7; the cost model's number of s-chunks and one
  * fewer / one more) and keeps the fastest in place of a shape set before -- or
  * the tile kernel, where that is the automatic choice (see sbp_set_launch) and
- * faster than every shape.  Above 1.75 million nodes, where it times the stage
- * kernel alone, the reverse sweep's right-hand sides keep their automatic
- * choice.  Writes the tile height and s-chunk length of the
+ * faster than every shape.  Where the automatic choice is the stage kernel it
+ * times that alone, and the reverse sweep's right-hand sides keep theirs.  Writes the tile height and s-chunk length of the
  * fastest shape and the time per evaluation (ms) of what it keeps to the
  * outputs (each may be NULL).  The state and time are not changed; call
  * it between steps.  Synchronises the stream.

@@ -118,6 +118,7 @@ struct sbp_ctx {
   bool shape_set = false;    // launch shape ty, zchunk of the caller's (sbp_set_launch)
   bool shape_tuned = false;  // and of sbp_autotune's, where the tile kernel was not the faster or not timed
   TileShape tile{};        // tile kernel's launch shape
+  bool tile_ok = false;    // tile_stage(): whether its stages are the tile kernel's by default
   // launch timing (sbp_set_profiling)
   bool prof = false;
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
@@ -400,46 +401,6 @@ int compute_metrics(sbp_ctx* h, const double* xyz) {
   return SBP_OK;
 }
 
-// balanced split of [0, N) into tiles of width <= W whose first and last tile
-// hold at least m points (so SBP closure rows never straddle a tile edge)
-std::vector<int> tile_bounds(int N, int W, int m) {
-  std::vector<int> b;
-  if (N <= W) return {0, N};
-  int T = (N + W - 1) / W;
-  for (int t = 0; t <= T; ++t) b.push_back((int)((long long)t * N / T));
-  if (b[1] - b[0] >= m && b[T] - b[T - 1] >= m) return b;
-  // fall back: full first and last tiles, balanced middle
-  b.assign(1, 0);
-  b.push_back(W);
-  const int mid = N - 2 * W;
-  if (mid > 0) {
-    const int Tm = (mid + W - 1) / W;
-    for (int t = 1; t <= Tm; ++t) b.push_back(W + (int)((long long)t * mid / Tm));
-  }
-  if (b.back() != N - W) b.push_back(N - W);
-  b.push_back(N);
-  return b;
-}
-
-// split of [0, N) along q into tiles of width <= 64 whose starts are
-// multiples of `align` points (128-byte lines), the first and last tile
-// holding at least m points
-std::vector<int> tile_bounds_aligned(int N, int align, int m) {
-  std::vector<int> b{0};
-  while (N - b.back() > 64) b.push_back(b.back() + 64);
-  b.push_back(N);
-  // a last tile narrower than m: move its start back by one line at a time
-  while (b.size() > 2 && b[b.size() - 1] - b[b.size() - 2] < m) {
-    const int s = b[b.size() - 2] - align;
-    if (s <= b[b.size() - 3]) break;
-    b[b.size() - 2] = s;
-  }
-  bool ok = b.size() >= 2;
-  for (std::size_t t = 0; t + 1 < b.size(); ++t) ok = ok && b[t + 1] - b[t] <= 64 && b[t + 1] > b[t];
-  ok = ok && (b.size() == 2 || (b[1] - b[0] >= m && b[b.size() - 1] - b[b.size() - 2] >= m));
-  return ok ? b : tile_bounds(N, 64, m);
-}
-
 int prepare_bounds(sbp_ctx* h) {
   if (!h->bounds_dirty) return SBP_OK;
   const Geometry& g = h->g;
@@ -449,36 +410,21 @@ int prepare_bounds(sbp_ctx* h) {
   // is a multiple of the tile height, also row nr - 1 so that no tile along
   // r is shorter than ty (for nq = 64 k + 1, nr = ty k + 1 every tile is full).
   h->ex = 1;
-  h->ey = ((g.nr - 1) % h->ty == 0 && g.nr - 1 >= 2 * h->ty) ? 1 : 0;
+  h->ey = edge_row(g.nr, h->ty);
   std::vector<int> xb = tile_bounds_aligned(g.nq - h->ex, line, h->cl.m);
   std::vector<int> yb = tile_bounds(g.nr - h->ey, h->ty, h->cl.m);
   h->nxt = (int)xb.size() - 1;
   h->nyt = (int)yb.size() - 1;
   int zc = h->zchunk;
   if (zc <= 0) {
-    // chunks along s: the s queues of a chunk start with r + q + 1 planes
-    // of warm-up, and the blocks run in waves of one block per compute unit;
-    // take the number of chunks that minimises waves x (planes + warm-up)
     int cus = 256;
     int dev = 0;
     if (hipGetDevice(&dev) == hipSuccess) {
       int v = 0;
       if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
     }
-    const long long cols = (long long)h->nxt * h->nyt;
-    const int warm = h->cl.r + h->cl.q + 1;
-    const int nzmax = std::max(1, g.ns / 8);
-    long long best = -1;
-    int bestnz = 1;
-    for (int nz = 1; nz <= nzmax; ++nz) {
-      const long long waves = (cols * nz + cus - 1) / cus;
-      const long long cost = waves * ((g.ns + nz - 1) / nz + warm);
-      if (best < 0 || cost < best) {
-        best = cost;
-        bestnz = nz;
-      }
-    }
-    zc = (g.ns + bestnz - 1) / bestnz;
+    const MarchSplit m = march_split((long long)h->nxt * h->nyt, g.ns, h->cl.r + h->cl.q + 1, cus);
+    zc = (g.ns + m.chunks - 1) / m.chunks;
   }
   zc = std::max(1, std::min(zc, g.ns));
   h->nzc = (g.ns + zc - 1) / zc;
@@ -494,19 +440,11 @@ int prepare_bounds(sbp_ctx* h) {
   return SBP_OK;
 }
 
-// Whether the grid's stages run as one tile-kernel launch each, else as the
-// stage kernel's march along s with the edge and penalty launches (always with
-// a launch shape of the caller's or plain addressing).  The tile kernel reads
-// the planes around a node again for every node, which costs little while the
-// caches hold them; the march reads them once, in a chain of planes whose
-// latency small grids cannot hide.  They meet between 1.6 and 2.1 million
-// nodes in both precisions (us per stage, tile and march: order 6 single
-// 1.44e6 nodes 96 and 120, 2.15e6 141 and 136; double 1.44e6 214 and 231,
-// 2.15e6 311 and 298; order 3 double 1.61e6 189 and 214).
-constexpr std::size_t kTileNodes = 1750000;
-
+// Whether the grid's stages run as one tile-kernel launch each (tile_stage),
+// else as the stage kernel's march along s with the edge and penalty launches
+// (always with a launch shape of the caller's or plain addressing).
 bool use_tile(const sbp_ctx* h) {
-  return !h->shape_set && !h->shape_tuned && !h->plain && h->g.n <= kTileNodes;
+  return !h->shape_set && !h->shape_tuned && !h->plain && h->tile_ok;
 }
 
 // The same for a right-hand side alone without penalties (the reverse sweep's).
@@ -515,12 +453,12 @@ bool use_tile(const sbp_ctx* h) {
 // million nodes (order 6, tile and march with its edge launch: 2.15e6 nodes 119
 // and 136 us, 4.17e6 nodes 43 us less, 7.19e6 13 us more; order 8 equal); in
 // double precision they take turns above kTileNodes.  sbp_autotune's shape does
-// not count above kTileNodes: it is the fastest of the march's, and the tile
-// kernel was not among what it timed.
+// not count where the automatic choice of a stage is the march: it is the
+// fastest of the march's, and the tile kernel was not among what it timed.
 constexpr std::size_t kTileRhsNodes = 4500000;
 
 bool use_tile_rhs(const sbp_ctx* h) {
-  return use_tile(h) || (h->dtype == SBP_F32 && !h->shape_set && !h->plain && h->g.n > kTileNodes &&
+  return use_tile(h) || (h->dtype == SBP_F32 && !h->shape_set && !h->plain && !h->tile_ok &&
                          h->g.n <= kTileRhsNodes);
 }
 
@@ -1964,6 +1902,7 @@ int sbp_init_grid(sbp_handle* out, int nq, int nr, int ns, const double* xyz, in
     delete h;
     return fail(SBP_EINVAL, "closure construction failed: %s", err);
   }
+  h->tile_ok = tile_stage({nq, nr, ns, order, h->cl.r, h->cl.q, h->esize, field_bytes(h)});
   {
     // closure rows: h D+ and h D- at the left end, then their negatives,
     // which are the right-end rows of h D+ and h D- against reversed columns

@@ -1,6 +1,83 @@
 #include "route.hpp"
 
+#include <algorithm>
+
 namespace sbp {
+
+std::vector<int> tile_bounds(int N, int W, int m) {
+  std::vector<int> b;
+  if (N <= W) return {0, N};
+  int T = (N + W - 1) / W;
+  for (int t = 0; t <= T; ++t) b.push_back((int)((long long)t * N / T));
+  if (b[1] - b[0] >= m && b[T] - b[T - 1] >= m) return b;
+  // fall back: full first and last tiles, balanced middle
+  b.assign(1, 0);
+  b.push_back(W);
+  const int mid = N - 2 * W;
+  if (mid > 0) {
+    const int Tm = (mid + W - 1) / W;
+    for (int t = 1; t <= Tm; ++t) b.push_back(W + (int)((long long)t * mid / Tm));
+  }
+  if (b.back() != N - W) b.push_back(N - W);
+  b.push_back(N);
+  return b;
+}
+
+std::vector<int> tile_bounds_aligned(int N, int align, int m) {
+  std::vector<int> b{0};
+  while (N - b.back() > 64) b.push_back(b.back() + 64);
+  b.push_back(N);
+  // a last tile narrower than m: move its start back by one line at a time
+  while (b.size() > 2 && b[b.size() - 1] - b[b.size() - 2] < m) {
+    const int s = b[b.size() - 2] - align;
+    if (s <= b[b.size() - 3]) break;
+    b[b.size() - 2] = s;
+  }
+  bool ok = b.size() >= 2;
+  for (std::size_t t = 0; t + 1 < b.size(); ++t) ok = ok && b[t + 1] - b[t] <= 64 && b[t + 1] > b[t];
+  ok = ok && (b.size() == 2 || (b[1] - b[0] >= m && b[b.size() - 1] - b[b.size() - 2] >= m));
+  return ok ? b : tile_bounds(N, 64, m);
+}
+
+int edge_row(int nr, int ty) { return (nr - 1) % ty == 0 && nr - 1 >= 2 * ty ? 1 : 0; }
+
+MarchSplit march_split(long long cols, int ns, int warm, int cus) {
+  MarchSplit best{1, -1};
+  for (int nz = 1; nz <= std::max(1, ns / 8); ++nz) {
+    const long long waves = (cols * nz + cus - 1) / cus;
+    const long long planes = waves * ((ns + nz - 1) / nz + warm);
+    if (best.planes < 0 || planes < best.planes) best = {nz, planes};
+  }
+  return best;
+}
+
+// The tile kernel reads the planes around a node again for every node, which
+// costs little while the caches hold them; the march reads them once, in a chain
+// of planes whose latency small grids cannot hide.  Near-cubic grids meet
+// between 1.6 and 2.1 million nodes (us per stage, tile and march: order 6
+// single 1.44e6 nodes 96 and 120, 2.15e6 141 and 136; double 1.44e6 214 and 231,
+// 2.15e6 311 and 298).  Below that the shape decides in single precision: the
+// tile kernel's time goes with the lanes of its tiles, used or not, at a rate
+// that depends on whether the fields fit the memory-side cache, the march's
+// with the planes of a compute unit.  The constants (us per million lanes, us
+// per plane) are fitted to 160 grids of 2e4 to 1.75e6 nodes, orders 2 to 8; the
+// rule then is nowhere more than 1 % slower than the march (by nodes alone:
+// order 8 at 65 x 65 x 400 181 and 127 us, at 117^3 153 and 142; order 4 at 40 x
+// 40 x 1000 177 and 149) and keeps all but 9 % of the tile kernel's gains.  In
+// double precision, where the march has two more launches and is bound by its
+// registers, the tile kernel is ahead on 85 of 87 grids, at most 3 % behind
+// (order 6 at 65 x 65 x 400: 262 and 253 us).
+bool tile_stage(const RouteGrid& g) {
+  if ((std::size_t)g.nq * g.nr * g.ns > kTileNodes) return false;
+  if (g.es == 8) return true;
+  static const double cached[7] = {36, 36, 42, 45, 48, 55, 80}, streamed[7] = {58, 60, 64, 67, 70, 74, 85};
+  const double lanes = 1e-6 * kTileNT * tile_shape(g.nq, g.nr, g.ns, g.order).ntiles;
+  const double tile = (g.bytes <= 270e6 ? cached : streamed)[g.order - 2] * lanes;
+  const long long cols = (long long)(tile_bounds_aligned(g.nq - 1, 128 / g.es, g.order).size() - 1) *
+                         (long long)(tile_bounds(g.nr - edge_row(g.nr, 8), 8, g.order).size() - 1);
+  const double march = 20.0 + (5.6 - 0.1 * g.order) * march_split(cols, g.ns, g.r + g.q + 1, 256).planes;
+  return tile <= march;
+}
 
 // us per stage of 16 shots of 64^3, order 4 (41.5 MB each in single precision),
 // with the work list and in groups of 1, 2, 3, 4, 6, 8 and 16: single

@@ -2,9 +2,45 @@
 // C++ (no HIP), so that they can be checked on the CPU alone.
 #pragma once
 
+#include <cstddef>
 #include <vector>
 
+#include "tile_shape.hpp"
+
 namespace sbp {
+
+// A grid as the rules see it: points, interior order (= closure rows), reach of
+// the stencil, bytes per value, bytes of its fields.
+struct RouteGrid {
+  int nq, nr, ns;
+  int order, r, q;
+  int es;
+  double bytes;
+};
+
+// Tile bounds of the stage kernel's march: a balanced split of [0, N) into
+// tiles of width <= W whose first and last tile hold at least m points (so that
+// SBP closure rows never straddle a tile edge), and one along q into tiles of
+// width <= 64 whose starts are multiples of `align` points (128-byte lines).
+std::vector<int> tile_bounds(int N, int W, int m);
+std::vector<int> tile_bounds_aligned(int N, int align, int m);
+// 1 if the edge kernel also takes the last r row (no tile of ty rows is then
+// shorter than that)
+int edge_row(int nr, int ty);
+
+// Chunks along s of a march over `cols` tiles: the s queues of a chunk start
+// with `warm` planes, and the blocks run in waves of one per compute unit; the
+// number of chunks that minimises the planes of a unit, waves x (planes + warm).
+struct MarchSplit {
+  int chunks;
+  long long planes;
+};
+MarchSplit march_split(long long cols, int ns, int warm, int cus);
+
+// Whether a stage of a single grid is faster as one launch of the tile kernel
+// than as the march with its edge and penalty launches.
+constexpr std::size_t kTileNodes = 1750000;
+bool tile_stage(const RouteGrid& g);
 
 // Cuts a batch's tile-kernel grids (the bytes of their fields, in the order in
 // which they run) into groups; returns the end of each.  A group's grids run

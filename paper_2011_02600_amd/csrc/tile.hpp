@@ -1,4 +1,4 @@
-// The tile stage kernel: launch shape (host) and launchers.
+// The tile stage kernel: launchers.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -7,11 +7,6 @@
 
 namespace sbp {
 
-// largest tile width (q) and height (r); threads per block
-constexpr int kTileW = 33, kTileH = 8, kTileNT = 256;
-
-// launch shape for nq x nr x ns points and m closure rows
-TileShape tile_shape(int nq, int nr, int ns, int m);
 // mode 0: Runge-Kutta stage; mode 1: the right-hand side into dq alone
 template <typename T>
 hipError_t launch_tile(int order, int mode, const StageArgs<T>& a, hipStream_t st);

@@ -1,7 +1,7 @@
 // Launch shape of the tile kernel.
 #include <algorithm>
 
-#include "tile.hpp"
+#include "tile_shape.hpp"
 
 namespace sbp {
 

@@ -54,8 +54,35 @@ static void groups() {
   }
 }
 
+// measured us per stage, tile kernel and march (one GPU, steps with a source)
+static void stages() {
+  struct Row {
+    int es, order, nq, nr, ns;
+    double tile, march;
+  };
+  static const Row rows[] = {
+      {4, 2, 97, 97, 97, 33.6, 79.5},      {4, 2, 40, 40, 1000, 155.3, 136.3},  {4, 2, 20, 260, 330, 173.4, 216.7},
+      {4, 4, 65, 65, 400, 71.9, 105.6},    {4, 4, 40, 40, 1000, 177.0, 148.8},  {4, 4, 20, 20, 4000, 197.5, 264.5},
+      {4, 6, 65, 65, 49, 18.0, 82.0},      {4, 6, 257, 257, 26, 102.8, 119.4},  {4, 6, 40, 40, 1000, 190.0, 161.3},
+      {4, 6, 1001, 40, 40, 94.8, 124.9},   {4, 7, 40, 40, 1000, 201.6, 167.7},  {4, 7, 513, 200, 16, 103.0, 143.2},
+      {4, 8, 65, 65, 65, 38.2, 93.8},      {4, 8, 97, 97, 97, 95.9, 105.7},     {4, 8, 65, 65, 400, 181.0, 126.9},
+      {4, 8, 120, 120, 120, 158.5, 146.0}, {4, 8, 20, 260, 260, 187.5, 249.3},  {4, 8, 40, 40, 1000, 230.9, 184.0},
+      {8, 3, 117, 117, 117, 186.2, 231.9}, {8, 6, 120, 120, 120, 247.5, 277.2}, {8, 8, 65, 65, 400, 350.4, 479.0},
+  };
+  static const int r[9] = {0, 0, 0, 1, 1, 2, 2, 3, 3}, q[9] = {0, 0, 2, 2, 3, 3, 4, 4, 5};
+  for (const Row& x : rows) {
+    const bool tile = tile_stage({x.nq, x.nr, x.ns, x.order, r[x.order], q[x.order], x.es, bytes(x.nq, x.nr, x.ns, x.es)});
+    if (tile != (x.tile < x.march)) {
+      std::printf("order %d %d x %d x %d (%d bytes): %s\n", x.order, x.nq, x.nr, x.ns, x.es, tile ? "tile" : "march");
+      ++bad;
+    }
+  }
+  check(!tile_stage({130, 130, 104, 6, 2, 4, 8, bytes(130, 130, 104, 8)}), "above the limit");
+}
+
 int main() {
   groups();
+  stages();
   std::printf(bad ? "%d failed\n" : "OK\n", bad);
   return bad ? 1 : 0;
 }

@@ -133,3 +133,27 @@ def test_refused_batch_advances_no_handle():
     for s in ss:
         assert s.time() == (0.0, 0)
         s.close()
+
+
+def test_grids_the_march_serves_better():
+    """Order 8 in single precision on 65 x 65 columns, which leave 39 % of the
+    tiles' lanes idle: stages are the march's, bit for bit those of a caller's
+    shape; its neighbour of 64 x 64 columns stays on the tile kernel."""
+    from paper_2011_02600_amd import sbp
+    print("case: grids the march serves better", flush=True)
+    for shape, march in (((200, 65, 65), True), ((200, 64, 64), False)):
+        ns, nr, nq = shape
+        xyz, med = W.warped_mesh(nq, nr, ns, seed=3, amp=0.02), W.random_medium(shape, 4)
+        Q = W.random_state(shape, 5, smooth=True)
+        out = []
+        for shaped in (False, True):
+            s = sbp.Solver(xyz, order=8, dtype="f32", gamma=[1, 0, 0.5, 0, -1, 1])
+            s.set_material(*med)
+            s.set_state(Q)
+            if shaped:
+                s.set_launch(8, 0)
+            s.step(2, 1e-4)
+            out.append(s.get_state().cpu().numpy())
+            s.close()
+        assert np.array_equal(*out) == march
+        assert rel_max(*(o.astype(np.float64) for o in out)) <= 1e-5

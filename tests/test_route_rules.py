@@ -14,7 +14,7 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2011_02600_amd", "csrc")
 def test_route_rules(tmp_path):
     exe = str(tmp_path / "route_check")
     cmd = ["g++", "-std=c++17", "-O1", "-Wall", "-I", CSRC, os.path.join(HERE, "host", "route_check.cpp"),
-           os.path.join(CSRC, "route.cpp"), "-o", exe]
+           os.path.join(CSRC, "route.cpp"), os.path.join(CSRC, "tile_shape.cpp"), "-o", exe]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
     r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
