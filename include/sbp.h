@@ -219,7 +219,10 @@ int sbp_set_graphs(sbp_handle h, int on);
  * sources or media ("shots") on grids of uneven size and mixed interior
  * orders.
  * Handles of up to 1.75 million nodes (without plain addressing or a launch
- * shape of the caller's, sbp_set_launch) run in groups small enough for a group's fields to stay in the memory-side cache,
+ * shape of the caller's, sbp_set_launch), if they are at least half of the
+ * batch's nodes, run in groups small enough for a group's fields to stay in
+ * the memory-side cache (those that an estimate gives to the larger handles'
+ * launches, mostly as too large for that cache, apart),
  * one group's steps after the other's; per stage and interior order of a
  * group one launch of the tile kernel covers all its grids, penalties and
  * sources included.  The larger handles run together: per stage one launch

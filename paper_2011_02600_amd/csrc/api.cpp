@@ -792,43 +792,21 @@ int device_cus() {
   return cus;
 }
 
-// the cost model's chunk length: waves of one block per compute unit times
-// the planes a block marches (its chunk plus the warm-up planes)
-int batch_cost_model_L(sbp_ctx** hs, int n) {
-  const int cus = device_cus();
-  int nsmax = 0;
-  for (int g = 0; g < n; ++g) nsmax = std::max(nsmax, hs[g]->g.ns);
-  long long best = -1;
-  int bestL = nsmax;
-  for (int L = nsmax; L >= 8; L = L * 3 / 4) {
-    long long tiles = 0, planes = 0;
-    for (int g = 0; g < n; ++g) {
-      const sbp_ctx* h = hs[g];
-      const int Lg = std::min(L, h->g.ns);
-      const int nz = (h->g.ns + Lg - 1) / Lg;
-      tiles += (long long)h->nxt * h->nyt * nz;
-      planes = std::max<long long>(planes, (h->g.ns + nz - 1) / nz + h->cl.r + h->cl.q + 1);
-    }
-    const long long cost = (tiles + cus - 1) / cus * planes;
-    if (best < 0 || cost < best) {
-      best = cost;
-      bestL = L;
-    }
-  }
-  return bestL;
+RouteGrid route_grid(const sbp_ctx* h) {
+  return {h->g.nq, h->g.nr, h->g.ns, h->order, h->cl.r, h->cl.q, h->esize, field_bytes(h)};
+}
+
+std::vector<RouteGrid> route_grids(sbp_ctx* const* hs, int n) {
+  std::vector<RouteGrid> v;
+  for (int g = 0; g < n; ++g) v.push_back(route_grid(hs[g]));
+  return v;
 }
 
 // applies chunk length L (0: the cost model's) and 8-row tiles to every grid
 int batch_apply_L(sbp_ctx** hs, int n, int L) {
+  if (L <= 0) L = list_chunk(route_grids(hs, n), device_cus());
   for (int g = 0; g < n; ++g) {
     hs[g]->ty = 8;
-    hs[g]->zchunk = 0;
-    hs[g]->bounds_dirty = true;
-    int rc = prepare_bounds(hs[g]);  // tiles across s (nxt, nyt)
-    if (rc) return rc;
-  }
-  if (L <= 0) L = batch_cost_model_L(hs, n);
-  for (int g = 0; g < n; ++g) {
     hs[g]->zchunk = std::min(L, hs[g]->g.ns);
     hs[g]->bounds_dirty = true;
     int rc = prepare_bounds(hs[g]);
@@ -1261,18 +1239,44 @@ int do_steps_group(sbp_ctx** hs, int n, int nsteps, const double* dt, bool tile)
 // whether a grid of a batch runs in a tile-kernel group: as use_tile, but a
 // shape that sbp_autotune chose for the grid alone does not count
 bool batch_tile(const sbp_ctx* h) { return !h->shape_set && !h->plain && h->g.n <= kTileNodes; }
-// Whether such grids leave the work list: they do if they are at least half of
-// the batch's nodes.  A few small grids beside large ones fill the list's gaps
-// instead (32 cubes of 65 to 193 points, 8 % of the nodes in small ones: all
-// in one list 11.57 shots/s, apart 11.27; eight grids of 65 to 129 points, 3/4
-// of the nodes in small ones: one list 96.5 ms, apart 86.5).
-bool batch_groups(sbp_ctx* const* hs, int n) {
-  std::size_t small = 0, all = 0;
+// The grids of a batch that run in tile-kernel groups (small, by rising size)
+// and those that run over the work list (large).  Small grids stay on the list
+// unless they are at least half of the batch's nodes: a few beside large ones
+// fill the list's gaps (32 cubes of 65 to 193 points, 8 % of the nodes in small
+// ones: all in one list 11.57 shots/s, apart 11.27; eight grids of 65 to 129
+// points, 3/4 of the nodes in small ones: one list 96.5 ms, apart 86.5).  And
+// those whose fields no group keeps in the cache, or which tile_stage would not
+// give the tile kernel, go back to it where list_us says so.
+void batch_split(sbp_ctx* const* hs, int n, std::vector<int>& small, std::vector<int>& large) {
+  std::size_t nodes = 0, all = 0;
   for (int g = 0; g < n; ++g) {
     all += hs[g]->g.n;
-    if (batch_tile(hs[g])) small += hs[g]->g.n;
+    if (batch_tile(hs[g])) nodes += hs[g]->g.n;
   }
-  return 2 * small >= all;
+  const bool apart = 2 * nodes >= all;
+  std::vector<int> open;
+  std::vector<RouteGrid> with, without;
+  double tile = 0.0;
+  for (int g = 0; g < n; ++g) {
+    const RouteGrid r = route_grid(hs[g]);
+    if (!apart || !batch_tile(hs[g])) {
+      large.push_back(g);
+      with.push_back(r);
+      without.push_back(r);
+    } else if (r.bytes > kGroupBytes || !hs[g]->tile_ok) {
+      open.push_back(g);
+      with.push_back(r);
+      tile += tile_us(r, kGroupBytes);
+    } else {
+      small.push_back(g);
+    }
+  }
+  if (!open.empty()) {
+    std::vector<int>& to = tile + list_us(without) <= list_us(with) ? small : large;
+    to.insert(to.end(), open.begin(), open.end());
+    std::sort(large.begin(), large.end());
+  }
+  std::stable_sort(small.begin(), small.end(), [&](int a, int b) { return hs[a]->g.n < hs[b]->g.n; });
 }
 
 // A batch's grids are independent, so it runs in groups, each all its steps
@@ -1285,9 +1289,7 @@ bool batch_groups(sbp_ctx* const* hs, int n) {
 template <typename T>
 int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
   std::vector<int> small, large;
-  const bool groups = batch_groups(hs, n);
-  for (int g = 0; g < n; ++g) (groups && batch_tile(hs[g]) ? small : large).push_back(g);
-  std::stable_sort(small.begin(), small.end(), [&](int a, int b) { return hs[a]->g.n < hs[b]->g.n; });
+  batch_split(hs, n, small, large);
   std::vector<sbp_ctx*> gh;
   std::vector<double> gd;
   auto run = [&](bool tile) -> int {
@@ -1327,10 +1329,10 @@ int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
 template <typename T>
 int do_autotune_batch(sbp_ctx** hs, int n, int reps, int* bestL, double* best_ms) {
   // the handles sbp_step_batch runs over the work list, if there are several
+  std::vector<int> small, listed;
+  batch_split(hs, n, small, listed);
   std::vector<sbp_ctx*> large;
-  const bool groups = batch_groups(hs, n);
-  for (int g = 0; g < n; ++g)
-    if (!groups || !batch_tile(hs[g])) large.push_back(hs[g]);
+  for (int g : listed) large.push_back(hs[g]);
   sbp_ctx** const all = hs;
   const int nall = n;
   if (large.size() > 1) {
@@ -1348,7 +1350,7 @@ int do_autotune_batch(sbp_ctx** hs, int n, int reps, int* bestL, double* best_ms
     BatchSettings keep(hs, n);
     int rc = batch_apply_L(hs, n, 0);
     if (rc) return rc;
-    const int L0 = batch_cost_model_L(hs, n);
+    const int L0 = list_chunk(route_grids(hs, n), device_cus());
     for (int L : {L0, L0 * 3 / 4, L0 * 3 / 2, L0 * 2, nsmax})
       if (L >= 8 && std::find(cands.begin(), cands.end(), std::min(L, nsmax)) == cands.end())
         cands.push_back(std::min(L, nsmax));
@@ -1902,7 +1904,7 @@ int sbp_init_grid(sbp_handle* out, int nq, int nr, int ns, const double* xyz, in
     delete h;
     return fail(SBP_EINVAL, "closure construction failed: %s", err);
   }
-  h->tile_ok = tile_stage({nq, nr, ns, order, h->cl.r, h->cl.q, h->esize, field_bytes(h)});
+  h->tile_ok = tile_stage(route_grid(h));
   {
     // closure rows: h D+ and h D- at the left end, then their negatives,
     // which are the right-end rows of h D+ and h D- against reversed columns

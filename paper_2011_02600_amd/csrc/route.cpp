@@ -1,6 +1,7 @@
 #include "route.hpp"
 
 #include <algorithm>
+#include <functional>
 
 namespace sbp {
 
@@ -51,6 +52,12 @@ MarchSplit march_split(long long cols, int ns, int warm, int cus) {
   return best;
 }
 
+// tiles of the stage kernel's march, 8 rows high, per plane
+static long long march_cols(const RouteGrid& g) {
+  return (long long)(tile_bounds_aligned(g.nq - 1, 128 / g.es, g.order).size() - 1) *
+         (long long)(tile_bounds(g.nr - edge_row(g.nr, 8), 8, g.order).size() - 1);
+}
+
 // The tile kernel reads the planes around a node again for every node, which
 // costs little while the caches hold them; the march reads them once, in a chain
 // of planes whose latency small grids cannot hide.  Near-cubic grids meet
@@ -70,13 +77,93 @@ MarchSplit march_split(long long cols, int ns, int warm, int cus) {
 bool tile_stage(const RouteGrid& g) {
   if ((std::size_t)g.nq * g.nr * g.ns > kTileNodes) return false;
   if (g.es == 8) return true;
-  static const double cached[7] = {36, 36, 42, 45, 48, 55, 80}, streamed[7] = {58, 60, 64, 67, 70, 74, 85};
-  const double lanes = 1e-6 * kTileNT * tile_shape(g.nq, g.nr, g.ns, g.order).ntiles;
-  const double tile = (g.bytes <= 270e6 ? cached : streamed)[g.order - 2] * lanes;
-  const long long cols = (long long)(tile_bounds_aligned(g.nq - 1, 128 / g.es, g.order).size() - 1) *
-                         (long long)(tile_bounds(g.nr - edge_row(g.nr, 8), 8, g.order).size() - 1);
-  const double march = 20.0 + (5.6 - 0.1 * g.order) * march_split(cols, g.ns, g.r + g.q + 1, 256).planes;
-  return tile <= march;
+  const double march = 20.0 + (5.6 - 0.1 * g.order) * march_split(march_cols(g), g.ns, g.r + g.q + 1, 256).planes;
+  return tile_us(g, 270e6) <= march;
+}
+
+double tile_us(const RouteGrid& g, double cache) {
+  static const double rate[2][2][7] = {{{36, 36, 42, 45, 48, 55, 80}, {58, 60, 64, 67, 70, 74, 85}},
+                                       {{82, 82, 90, 103, 112, 120, 130}, {99, 105, 109, 114, 130, 130, 142}}};
+  return rate[g.es == 8][g.bytes > cache][g.order - 2] * 1e-6 * kTileNT *
+         tile_shape(g.nq, g.nr, g.ns, g.order).ntiles;
+}
+
+int list_chunk(const std::vector<RouteGrid>& grids, int cus) {
+  int nsmax = 0;
+  for (const RouteGrid& g : grids) nsmax = std::max(nsmax, g.ns);
+  long long best = -1;
+  int bestL = nsmax;
+  for (int L = nsmax; L >= 8; L = L * 3 / 4) {
+    long long tiles = 0, planes = 0;
+    for (const RouteGrid& g : grids) {
+      const int Lg = std::min(L, g.ns), nz = (g.ns + Lg - 1) / Lg;
+      tiles += march_cols(g) * nz;
+      planes = std::max<long long>(planes, (g.ns + nz - 1) / nz + g.r + g.q + 1);
+    }
+    const long long cost = (tiles + cus - 1) / cus * planes;
+    if (best < 0 || cost < best) {
+      best = cost;
+      bestL = L;
+    }
+  }
+  return bestL;
+}
+
+// The list's blocks in the order in which the launch takes them: 8 segments of
+// equal cost (grids largest first), one per XCD, whose 32 compute units take
+// each the next longest block; an edge block counts as 4 planes.  The time is
+// that of the last unit, at rates fitted to 80 batches, most of two to five
+// grids whose fields do not fit the cache: there the list was from 1.34 times
+// as fast as the tile kernel to 1.9 times as slow.  Choosing by the estimates
+// costs 0.5 % on average against the better of both (always the tile kernel
+// 2.4 %; us per stage, tile kernel and list: 3 of 117^3, order 6, single 388 and
+// 347, double 715 and 607; 8 of 65 x 65 x 200, order 8, single 807 and 603).  With
+// orders that take launches per order instead of the list (7 and 8 in double
+// precision) the tile kernel was ahead throughout, by 1.1 to 3 times.
+double list_us(const std::vector<RouteGrid>& grids) {
+  if (grids.empty()) return 0.0;
+  int order = 0;
+  std::vector<RouteGrid> by = grids;
+  std::stable_sort(by.begin(), by.end(), [](const RouteGrid& a, const RouteGrid& b) {
+    return (long long)a.nq * a.nr * a.ns > (long long)b.nq * b.nr * b.ns;
+  });
+  const int L = list_chunk(grids, 256);
+  struct Run {  // `n` blocks of `planes` planes
+    long long n;
+    int planes;
+  };
+  std::vector<Run> runs;
+  long long total = 0;
+  for (const RouteGrid& g : by) {
+    order = std::max(order, g.order);
+    const int Lg = std::min(L, g.ns), nz = (g.ns + Lg - 1) / Lg;
+    const int edge = (g.nr + 63) / 64 + (edge_row(g.nr, 8) ? (g.nq - 1 + 63) / 64 : 0);
+    runs.push_back({march_cols(g) * nz, (g.ns + nz - 1) / nz + g.r + g.q + 1});
+    runs.push_back({(long long)edge * ((g.ns + 7) / 8), 4});
+    for (std::size_t i = runs.size() - 2; i < runs.size(); ++i) total += runs[i].n * runs[i].planes;
+  }
+  if (grids[0].es == 8 && order >= 7) return 1e30;
+  long long last = 0, acc = 0;
+  std::size_t at = 0;
+  for (int x = 0; x < 8; ++x) {
+    std::vector<Run> part;
+    for (const long long goal = total * (x + 1) / 8; at < runs.size() && acc < goal;) {
+      const long long n = std::min(runs[at].n, (goal - acc + runs[at].planes - 1) / runs[at].planes);
+      part.push_back({n, runs[at].planes});
+      acc += n * runs[at].planes;
+      if ((runs[at].n -= n) == 0) ++at;
+    }
+    std::stable_sort(part.begin(), part.end(), [](const Run& a, const Run& b) { return a.planes > b.planes; });
+    std::vector<long long> unit(32, 0);  // a heap, the earliest first
+    for (const Run& r : part)
+      for (long long i = 0; i < r.n; ++i) {
+        std::pop_heap(unit.begin(), unit.end(), std::greater<long long>());
+        unit.back() += r.planes;
+        std::push_heap(unit.begin(), unit.end(), std::greater<long long>());
+      }
+    last = std::max(last, *std::max_element(unit.begin(), unit.end()));
+  }
+  return grids[0].es == 8 ? 150.0 + 8.0 * last : (order == 8 ? 150.0 + 6.6 * last : 60.0 + 5.1 * last);
 }
 
 // us per stage of 16 shots of 64^3, order 4 (41.5 MB each in single precision),

@@ -42,6 +42,17 @@ MarchSplit march_split(long long cols, int ns, int warm, int cus);
 constexpr std::size_t kTileNodes = 1750000;
 bool tile_stage(const RouteGrid& g);
 
+// Estimated us per stage of the tile kernel on a grid; `cache`: bytes of fields
+// that stay in the memory-side cache.
+double tile_us(const RouteGrid& g, double cache);
+
+// Planes per s-chunk of a batch's work list over `cus` compute units: the length
+// that minimises waves of one block per unit times the planes of a block (its
+// chunk plus the warm-up planes).
+int list_chunk(const std::vector<RouteGrid>& grids, int cus);
+// Estimated us per stage of a batch over the work list (no grids: 0).
+double list_us(const std::vector<RouteGrid>& grids);
+
 // Cuts a batch's tile-kernel grids (the bytes of their fields, in the order in
 // which they run) into groups; returns the end of each.  A group's grids run
 // all their steps before the next group's, in launches they share, so its

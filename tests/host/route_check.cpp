@@ -80,9 +80,42 @@ static void stages() {
   check(!tile_stage({130, 130, 104, 6, 2, 4, 8, bytes(130, 130, 104, 8)}), "above the limit");
 }
 
+// measured us per stage of k grids in groups of the tile kernel and on the work
+// list, where no group keeps their fields in the cache
+static void lists() {
+  struct Row {
+    int es, order, nq, nr, ns, k;
+    double tile, list;
+  };
+  static const Row rows[] = {
+      {8, 6, 103, 91, 109, 3, 526, 464},
+      {4, 4, 96, 109, 149, 2, 126, 240},
+      {8, 6, 109, 98, 89, 4, 620, 537},
+      {8, 6, 101, 108, 100, 4, 755, 649},
+      {8, 6, 108, 112, 98, 4, 747, 658},
+      {8, 4, 133, 173, 32, 4, 312, 569},
+      {8, 6, 105, 91, 103, 5, 832, 680},
+      {4, 6, 117, 117, 117, 3, 388, 347},
+      {8, 6, 117, 117, 117, 3, 715, 607},
+      {8, 6, 113, 113, 113, 4, 886, 713},
+      {4, 8, 65, 65, 200, 8, 807, 603},
+  };
+  static const int r[9] = {0, 0, 0, 1, 1, 2, 2, 3, 3}, q[9] = {0, 0, 2, 2, 3, 3, 4, 4, 5};
+  for (const Row& x : rows) {
+    const RouteGrid g{x.nq, x.nr, x.ns, x.order, r[x.order], q[x.order], x.es, bytes(x.nq, x.nr, x.ns, x.es)};
+    if ((x.k * tile_us(g, kGroupBytes) <= list_us(std::vector<RouteGrid>(x.k, g))) != (x.tile < x.list)) {
+      std::printf("%d of %d x %d x %d, order %d (%d bytes): tile %.0f list %.0f\n", x.k, x.nq, x.nr, x.ns, x.order, x.es,
+                  x.k * tile_us(g, kGroupBytes), list_us(std::vector<RouteGrid>(x.k, g)));
+      ++bad;
+    }
+  }
+  check(list_us({}) == 0.0, "empty list");
+}
+
 int main() {
   groups();
   stages();
+  lists();
   std::printf(bad ? "%d failed\n" : "OK\n", bad);
   return bad ? 1 : 0;
 }
