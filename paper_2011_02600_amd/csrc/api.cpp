@@ -211,7 +211,7 @@ BatchRegion batch_region() {
     o = align256(o + bytes);
     return at;
   };
-  r.stage = take((std::size_t)10 * kMaxBatch * sizeof(StageArgs<double>));
+  r.stage = take((std::size_t)10 * kMaxBatch * sizeof(TileArgs<double>));
   r.first = take((std::size_t)2 * kMaxGroups * (kMaxBatch + 1) * sizeof(int));
   r.src = take((std::size_t)10 * kMaxBatch * sizeof(SourceArgs<double>));
   r.src_first = take((std::size_t)(kMaxBatch + 1) * sizeof(int));
@@ -512,10 +512,19 @@ StageArgs<T> stage_args(sbp_ctx* h) {
   a.scl = (T*)(h->ws + h->off_scl);
   a.eqc = sizeof(T) == 4 ? (T*)(h->ws + h->off_eqc) : nullptr;
   a.nsrc = 0;
-  a.src_stride = kMaxSources;
-  a.tw = (const T*)(h->ws + h->off_tw);
-  a.tile = h->tile;
   return a;
+}
+
+// the tile kernel's arguments for a stage; part: see TileShape
+template <typename T>
+TileArgs<T> tile_args(sbp_ctx* h, const StageArgs<T>& a, int part = 0) {
+  TileArgs<T> t{a};
+  t.src_stride = kMaxSources;
+  t.src_off = 0;
+  t.tw = (const T*)(h->ws + h->off_tw);
+  t.tile = h->tile;
+  t.tile.part = part;
+  return t;
 }
 
 // point sources of stage k at time tstage (g(t) evaluated on the host in double)
@@ -615,13 +624,10 @@ int run_stage(sbp_ctx* h, StageArgs<T>& a, int k, double dt, double tstage, bool
   if (use_tile(h)) {
     // timed, the launch is split: the nodes sbp_profile reports, then the
     // last q column and r row
-    if (prof) a.tile.part = 1;
-    HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, a, st));
+    HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, tile_args<T>(h, a, prof ? 1 : 0), st));
     if (prof) {
       HIPCHK(hipEventRecord(h->ev[1], st));
-      a.tile.part = 2;
-      HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, a, st));
-      a.tile.part = 0;
+      HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, tile_args<T>(h, a, 2), st));
     }
   } else {
     HIPCHK(launch_stage<T>(h->order, h->ty, a, st));
@@ -909,11 +915,7 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
     for (int k = 0; k < 5; ++k)
       for (int p = 0; p < 2; ++p) {
         StageArgs<T> e = stage_entry<T>(h, a, k, h->cur ^ p, dt[g], rhs_only);
-        if (P.tile) {
-          put_sources<T>(h, e, k, dt[g], 0.0, rhs_only, (const StepClock*)(base + R.clock));
-          e.src_stride = n * kMaxSources;
-          e.src_off = g * kMaxSources;
-        }
+        if (P.tile) put_sources<T>(h, e, k, dt[g], 0.0, rhs_only, (const StepClock*)(base + R.clock));
         sa[(std::size_t)(k * 2 + p) * kMaxBatch + g] = e;
       }
   }
@@ -943,9 +945,20 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
     if (P.ngroups > kMaxGroups) return fail(SBP_EINVAL, "too many interior orders in a batch");
     // the grouped kernels index the argument table in group order
     std::vector<StageArgs<T>> sg((std::size_t)10 * kMaxBatch);
+    std::vector<TileArgs<T>> tg(P.tile ? sg.size() : 0);
     for (int e = 0; e < 10; ++e)
-      for (int q = 0; q < n; ++q) sg[(std::size_t)e * kMaxBatch + q] = sa[(std::size_t)e * kMaxBatch + P.ord[q]];
-    HIPCHK(hipMemcpyAsync(base + R.stage, sg.data(), sg.size() * sizeof(StageArgs<T>), hipMemcpyHostToDevice, st));
+      for (int q = 0; q < n; ++q) {
+        const std::size_t at = (std::size_t)e * kMaxBatch + q;
+        sg[at] = sa[(std::size_t)e * kMaxBatch + P.ord[q]];
+        if (!P.tile) continue;
+        tg[at] = tile_args<T>(hs[P.ord[q]], sg[at]);
+        tg[at].src_stride = n * kMaxSources;
+        tg[at].src_off = P.ord[q] * kMaxSources;
+      }
+    if (P.tile)
+      HIPCHK(hipMemcpyAsync(base + R.stage, tg.data(), tg.size() * sizeof(TileArgs<T>), hipMemcpyHostToDevice, st));
+    else
+      HIPCHK(hipMemcpyAsync(base + R.stage, sg.data(), sg.size() * sizeof(StageArgs<T>), hipMemcpyHostToDevice, st));
     std::vector<int> firsts((std::size_t)2 * kMaxGroups * (kMaxBatch + 1), 0);
     P.sblocks.assign(P.ngroups, 0);
     P.eblocks.assign(P.ngroups, 0);
@@ -957,7 +970,7 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
         const StageArgs<T> a = stage_args<T>(hs[P.ord[q]]);
         fs[q - P.gstart[G]] = ts;
         fe[q - P.gstart[G]] = te;
-        ts += P.tile ? a.tile.ntiles : a.ntiles;
+        ts += P.tile ? hs[P.ord[q]]->tile.ntiles : a.ntiles;
         te += edge_blocks(a);
       }
       fs[P.gstart[G + 1] - P.gstart[G]] = ts;
@@ -1067,8 +1080,8 @@ int batch_stage_launch(sbp_ctx** hs, const BatchPlan<T>& P, int k, int e, hipStr
   const int* dfirst = (const int*)(base + R.first);
   if (P.tile) {
     for (int G = 0; G < P.ngroups; ++G) {
-      BatchArgs<T> b{};
-      b.args = dsa + P.gstart[G];
+      BatchArgs<T, TileArgs<T>> b{};
+      b.args = (const TileArgs<T>*)(base + R.stage) + (std::size_t)e * kMaxBatch + P.gstart[G];
       b.n = P.gstart[G + 1] - P.gstart[G];
       b.first = dfirst + (std::size_t)(2 * G) * (kMaxBatch + 1);
       b.total = P.sblocks[G];
@@ -1587,7 +1600,7 @@ int stage_explicit(sbp_ctx* h, const StageArgs<T>& base, int k, double dt, doubl
   if (!sources) b.nsrc = 0;
   const bool bare = rhs_only && !sat && !sources;
   if (bare ? use_tile_rhs(h) : use_tile(h)) {
-    HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, b, h->stream));
+    HIPCHK(launch_tile<T>(h->order, rhs_only ? 1 : 0, tile_args<T>(h, b), h->stream));
   } else {
     HIPCHK(launch_stage<T>(h->order, h->ty, b, h->stream));
     HIPCHK(edge_and_penalties<T>(h, b, h->stream));

@@ -161,16 +161,18 @@ __device__ __forceinline__ void node_rates(const T u[3][3], const T dv[3], const
 
 // ---------------------------------------------------------------------------
 // the point-source increments dt g(t) w M of node (i, j, k) (stress
-// components), summed over the sources whose stencil holds it
+// components), summed over the sources whose stencil holds it; stride, off: rows
+// of the source-time table and the grid's first entry in one
 template <typename T>
-__device__ __forceinline__ void source_add(const StageArgs<T>& A, int i, int j, int k, T add[6]) {
+__device__ __forceinline__ void source_add(const StageArgs<T>& A, int i, int j, int k, T add[6],
+                                           int stride = kMaxSources, int off = 0) {
   const int w = A.src_w;
   for (int s = 0; s < A.nsrc; ++s) {
     const int dk = k - A.src_k0[s], dj = j - A.src_j0[s], di = i - A.src_i0[s];
     if ((unsigned)dk < (unsigned)w && (unsigned)dj < (unsigned)w && (unsigned)di < (unsigned)w) {
       const T gdt = A.src_clock
                         ? static_cast<const T*>(A.src_clock->gtab)[((std::size_t)A.src_clock->step * 5 + A.src_stage) *
-                                                                       A.src_stride + A.src_off + s]
+                                                                       stride + off + s]
                         : A.src_gdt[s];
       const T* wm =
           A.src_wm + ((std::size_t)s * kMaxSrcWidth * kMaxSrcWidth * kMaxSrcWidth + (dk * w + dj) * w + di) * 6;

@@ -59,7 +59,7 @@ struct TilePoint {
 
 // MODE 0: Runge-Kutta stage; 1: the right-hand side into dq
 template <typename T, int ORDER, int MODE>
-__device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile, char* lds) {
+__device__ __forceinline__ void tile_body(const TileArgs<T>& A, const int tile, char* lds) {
   using S = Stencil<ORDER>;
   using L = TileLds<T, ORDER>;
   using P = TilePoint<T>;
@@ -416,7 +416,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
     if (k == 0 || k == ns - 1) face(2, k != 0, (std::size_t)j * nq + i);
   }
   T sadd[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-  if (nsrc > 0) source_add(A, i, j, k, sadd);
+  if (nsrc > 0) source_add(A, i, j, k, sadd, A.src_stride, A.src_off);
 #pragma unroll
   for (int c = 0; c < 9; ++c) {
     T d = dt * rate[c];
@@ -429,7 +429,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<T>& A, const int tile,
 }
 
 template <typename T, int ORDER, int MODE>
-__global__ __launch_bounds__(kTileNT, sizeof(T) == 4 && ORDER <= 6 ? 3 : 2) void tile_kernel(const StageArgs<T> A) {
+__global__ __launch_bounds__(kTileNT, sizeof(T) == 4 && ORDER <= 6 ? 3 : 2) void tile_kernel(const TileArgs<T> A) {
   __shared__ __align__(16) char lds[TileLds<T, ORDER>::bytes];
   // consecutive tiles on the same XCD
   const int per = gridDim.x >> 3;
@@ -439,24 +439,24 @@ __global__ __launch_bounds__(kTileNT, sizeof(T) == 4 && ORDER <= 6 ? 3 : 2) void
 // the tiles of several grids (a Runge-Kutta stage)
 template <typename T, int ORDER>
 __global__ __launch_bounds__(kTileNT, sizeof(T) == 4 && ORDER <= 6 ? 3 : 2) void tile_kernel_batch(
-    const BatchArgs<T> B) {
+    const BatchArgs<T, TileArgs<T>> B) {
   __shared__ __align__(16) char lds[TileLds<T, ORDER>::bytes];
   const int per = gridDim.x >> 3;
   const int item = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (item >= B.total) return;
   const int g = batch_find(B.first, B.n, item);
-  const StageArgs<T>& A = B.args[g];
+  const TileArgs<T>& A = B.args[g];
   tile_body<T, ORDER, 0>(A, item - B.first[g], lds);
 }
 
 template <typename T, int ORDER>
-hipError_t launch_bt(const BatchArgs<T>& b, hipStream_t st) {
+hipError_t launch_bt(const BatchArgs<T, TileArgs<T>>& b, hipStream_t st) {
   hipLaunchKernelGGL((tile_kernel_batch<T, ORDER>), dim3((b.total + 7) / 8 * 8), dim3(kTileNT), 0, st, b);
   return hipGetLastError();
 }
 
 template <typename T, int ORDER>
-hipError_t launch_t(int mode, const StageArgs<T>& a, hipStream_t st) {
+hipError_t launch_t(int mode, const TileArgs<T>& a, hipStream_t st) {
   const int nb = (a.tile.ntiles + 7) / 8 * 8;
   if (mode == 0)
     hipLaunchKernelGGL((tile_kernel<T, ORDER, 0>), dim3(nb), dim3(kTileNT), 0, st, a);
@@ -482,7 +482,7 @@ std::size_t scratch_t() {
 }  // namespace
 
 template <typename T>
-hipError_t launch_tile(int order, int mode, const StageArgs<T>& a, hipStream_t st) {
+hipError_t launch_tile(int order, int mode, const TileArgs<T>& a, hipStream_t st) {
   switch (order) {
     case 2: return launch_t<T, 2>(mode, a, st);
     case 3: return launch_t<T, 3>(mode, a, st);
@@ -496,7 +496,7 @@ hipError_t launch_tile(int order, int mode, const StageArgs<T>& a, hipStream_t s
 }
 
 template <typename T>
-hipError_t launch_tile_batch(int order, const BatchArgs<T>& b, hipStream_t st) {
+hipError_t launch_tile_batch(int order, const BatchArgs<T, TileArgs<T>>& b, hipStream_t st) {
   switch (order) {
     case 2: return launch_bt<T, 2>(b, st);
     case 3: return launch_bt<T, 3>(b, st);
@@ -524,12 +524,12 @@ std::size_t tile_scratch(int order) {
 }
 
 #ifdef SBP_TILE_F64
-template hipError_t launch_tile<double>(int, int, const StageArgs<double>&, hipStream_t);
-template hipError_t launch_tile_batch<double>(int, const BatchArgs<double>&, hipStream_t);
+template hipError_t launch_tile<double>(int, int, const TileArgs<double>&, hipStream_t);
+template hipError_t launch_tile_batch<double>(int, const BatchArgs<double, TileArgs<double>>&, hipStream_t);
 template std::size_t tile_scratch<double>(int);
 #else
-template hipError_t launch_tile<float>(int, int, const StageArgs<float>&, hipStream_t);
-template hipError_t launch_tile_batch<float>(int, const BatchArgs<float>&, hipStream_t);
+template hipError_t launch_tile<float>(int, int, const TileArgs<float>&, hipStream_t);
+template hipError_t launch_tile_batch<float>(int, const BatchArgs<float, TileArgs<float>>&, hipStream_t);
 template std::size_t tile_scratch<float>(int);
 #endif
 
