@@ -1775,10 +1775,11 @@ hipError_t launch_source(const SourceArgs<T>& s, int nsrc, hipStream_t st) {
 template <typename T>
 hipError_t launch_record(const T* q, std::size_t field, const long long* off, int nrec, T* out, StepClock* clock,
                          hipStream_t st) {
-  // up to 4096 receivers in one block that ticks the clock as well: a launch of
-  // its own for the tick is 4.9 us of every step, four rounds of one block cost
-  // less
-  if (nrec <= 4096) {
+  // up to 640 receivers in one block that ticks the clock as well, more in
+  // several blocks and a launch for the tick: us per step of 40^3 with one block
+  // and with two launches, 1 receiver 63.4 and 65.2, 640 65.4 and 66.0, 768 66.6
+  // and 66.2, 4096 79.1 and 67.8 (24^3 and 97^3 meet there too)
+  if (nrec <= 640) {
     hipLaunchKernelGGL(record_kernel<T>, dim3(1), dim3(nrec <= 256 ? 256 : 1024), 0, st, q, field, off, nrec, out,
                        clock, 1);
     return hipGetLastError();

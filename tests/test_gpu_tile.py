@@ -157,3 +157,32 @@ def test_grids_the_march_serves_better():
             s.close()
         assert np.array_equal(*out) == march
         assert rel_max(*(o.astype(np.float64) for o in out)) <= 1e-5
+
+
+@pytest.mark.parametrize("nrec", [1, 256, 257, 640, 641, 5000])
+def test_receivers_in_one_block_and_in_several(nrec):
+    """The recorded values are the state's, step after step, and the steps go on
+    with their own source-time factors, on both sides of the receivers' launch
+    that also ticks the step clock."""
+    from paper_2011_02600_amd import sbp
+    print("case: %d receivers" % nrec, flush=True)
+    nq, nr, ns = 33, 24, 21
+    rec = np.random.default_rng(nrec).integers(0, (nq, nr, ns), size=(nrec, 3))
+    s = sbp.Solver(W.warped_mesh(nq, nr, ns, seed=2, amp=0.02), order=4, dtype="f32", gamma=[1, 0, 0.5, 0, -1, 1])
+    s.set_material(*W.random_medium((ns, nr, nq), 3))
+    s.add_source((0.4, 0.5, 0.5), (1.0, 0.5, 0.2, 0.1, 0.0, 0.3), 0, 30.0, 0.002)
+    q = W.random_state((ns, nr, nq), 4, smooth=True)
+    s.set_state(q, 0.0)
+    tr = s.record(rec, 4)
+    s.step(4, 1e-3)
+    got, end = tr.cpu().numpy(), s.get_state().cpu().numpy()
+    s.set_state(q, 0.0)
+    s.record(rec, 4)
+    for n in range(4):
+        s.step(1, 1e-3)
+        q1 = s.get_state().cpu().numpy()
+        want = q1[:3, rec[:, 2], rec[:, 1], rec[:, 0]].T
+        # (a single step's source time is n dt summed up, not multiplied: one rounding)
+        assert np.abs(got[n] - want).max() <= 1e-6 * np.abs(q1[:3]).max(), n
+    assert np.abs(q1 - end).max() <= 1e-6 * np.abs(end).max()
+    s.close()
