@@ -921,12 +921,15 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
   }
   // wait for work of an earlier call that may still read the tables
   HIPCHK(hipStreamSynchronize(st));
-  HIPCHK(hipMemcpyAsync(base + R.stage, sa.data(), sa.size() * sizeof(StageArgs<T>), hipMemcpyHostToDevice, st));
+  // (the host tables, until the copies are waited for)
+  std::vector<BatchItem> items;
+  std::vector<int> seg, firsts;
+  std::vector<StageArgs<T>> sg;
+  std::vector<TileArgs<T>> tg;
   if (P.worklist) {
-    std::vector<BatchItem> items;
-    std::vector<int> seg;
     int rc = batch_items<T>(hs, n, items, seg);
     if (rc) return rc;
+    HIPCHK(hipMemcpyAsync(base + R.stage, sa.data(), sa.size() * sizeof(StageArgs<T>), hipMemcpyHostToDevice, st));
     P.maxseg = 0;
     for (int x = 0; x < 8; ++x) P.maxseg = std::max(P.maxseg, seg[x + 1] - seg[x]);
     HIPCHK(hipMemcpyAsync(base + R.items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice, st));
@@ -944,8 +947,8 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
     P.gstart.push_back(n);
     if (P.ngroups > kMaxGroups) return fail(SBP_EINVAL, "too many interior orders in a batch");
     // the grouped kernels index the argument table in group order
-    std::vector<StageArgs<T>> sg((std::size_t)10 * kMaxBatch);
-    std::vector<TileArgs<T>> tg(P.tile ? sg.size() : 0);
+    sg.resize((std::size_t)10 * kMaxBatch);
+    tg.resize(P.tile ? sg.size() : 0);
     for (int e = 0; e < 10; ++e)
       for (int q = 0; q < n; ++q) {
         const std::size_t at = (std::size_t)e * kMaxBatch + q;
@@ -959,7 +962,7 @@ int batch_upload(sbp_ctx** hs, int n, const double* dt, bool rhs_only, BatchPlan
       HIPCHK(hipMemcpyAsync(base + R.stage, tg.data(), tg.size() * sizeof(TileArgs<T>), hipMemcpyHostToDevice, st));
     else
       HIPCHK(hipMemcpyAsync(base + R.stage, sg.data(), sg.size() * sizeof(StageArgs<T>), hipMemcpyHostToDevice, st));
-    std::vector<int> firsts((std::size_t)2 * kMaxGroups * (kMaxBatch + 1), 0);
+    firsts.assign((std::size_t)2 * kMaxGroups * (kMaxBatch + 1), 0);
     P.sblocks.assign(P.ngroups, 0);
     P.eblocks.assign(P.ngroups, 0);
     for (int G = 0; G < P.ngroups; ++G) {
