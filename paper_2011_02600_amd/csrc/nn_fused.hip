@@ -15,8 +15,8 @@
 // a lane's four tiles are four consecutive x: 16-byte loads and stores.
 //
 // 8 media of 64^3, 32 channels, 8 modes, 4 layers (forward, loss, backward):
-// 6.67 -> 1.91 ms; one medium forward 386 -> 159 us (line_forward 28 us a layer,
-// its 67 MB at 2.4 TB/s).
+// 6.67 -> 1.91 ms; one medium forward 386 -> 159 us (line_forward 28 us a layer:
+// 101 MB, h read, z and h written, at 3.6 TB/s).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -165,8 +165,12 @@ __device__ __forceinline__ bf16x8 inverse_load(const LineArgs& A, const float* i
   if (c < A.C && k0 < A.m) {
     const float* const p = i1 + 16 * i * cs;
     const unsigned lo = (lane & 15) * (unsigned)cs + k0;
-    if (A.m == 8) {
-      const f32x4 v0 = ld4(p, lo), v1 = ld4(p + 4, lo);
+    // (rows of a multiple of 4 values start on 16 bytes; loads per value instead:
+    // forward pass of 4 media of 64^3, 32 channels, m = 12 458 -> 483 us, m = 16
+    // 525 -> 564)
+    if (A.m % 4 == 0) {
+      f32x4 v0 = ld4(p, lo), v1 = {0.f, 0.f, 0.f, 0.f};
+      if (k0 + 4 < A.m) v1 = ld4(p + 4, lo);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         a[e] = (__bf16)v0[e];
@@ -227,7 +231,11 @@ __device__ __forceinline__ void transform_x(const LineArgs& A, const __bf16* lds
 
 // ---- forward: z_l = T^T(..) + W h_l + b, h_{l+1} = gelu(z_l), t1 = its x
 // transform; LIFT_ONLY: t1 of h_0 = w x + b alone
-// FULL: n = 64 and C = 16 CT, no masks
+// FULL: lines and channels fill the tiles (n = 64 and C = 16 CT), no masks.
+// Forward and backward of 4 media of 64^3, 8 modes, with and without: 16 channels
+// 738 and 764 us, 32 1124 and 1208, 48 1642 and 1715, 64 2230 and 2305, though
+// the backward pass spills more at 64 (at 48 the forward pass alone is 692 and
+// 663, for one medium 234 and 251)
 template <int CT, int KS, int KX, bool LIFT_ONLY, bool FULL>
 __global__ __launch_bounds__(64 * kWaves, CT <= 2 ? 4 : 2) void line_forward_kernel(const LineArgs A) {
   __shared__ __align__(16) __bf16 lds_all[kWaves][16 * CT * kLinePitch];
