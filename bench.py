@@ -64,7 +64,8 @@ CSRC = os.path.join(ROOT, "paper_2011_02600_amd", "csrc")
 
 
 # sources that decide the stage kernel's code, launch shape and data layout
-STAGE_SOURCES = ("api.cpp", "internal.hpp", "kernels.hip", "kernels.hpp", "penalty.hpp")
+STAGE_SOURCES = ("api.cpp", "internal.hpp", "kernels.hip", "kernels.hpp", "penalty.hpp", "route.cpp", "route.hpp",
+                 "stencil.hpp")
 
 
 def kernel_sha():

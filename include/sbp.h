@@ -364,8 +364,11 @@ int sbp_energy(sbp_handle h, double* E);
  * tile kernel, which has no launch shape (in SBP_F32 unless an estimate from
  * its shape and order favours the stage kernel); with it the stage kernel
  * runs, with the shape given.
- * Does not change results beyond floating-point summation order (it does
- * not change it at all: every node is computed by the same instructions).
+ * Results are bitwise those of any other zchunk at the same ty (every node is
+ * computed by the same instructions) and agree to rounding between tile
+ * heights and between the stage kernel and the tile kernel.  sbp_autotune
+ * gives the choice back to the library; as it keeps what it times fastest, the
+ * last bits may then depend on its timings.
  */
 int sbp_set_launch(sbp_handle h, int ty, int zchunk);
 

@@ -90,14 +90,19 @@ double tile_us(const RouteGrid& g, double cache) {
 
 int list_chunk(const std::vector<RouteGrid>& grids, int cus) {
   int nsmax = 0;
-  for (const RouteGrid& g : grids) nsmax = std::max(nsmax, g.ns);
+  std::vector<long long> cols;
+  for (const RouteGrid& g : grids) {
+    nsmax = std::max(nsmax, g.ns);
+    cols.push_back(march_cols(g));
+  }
   long long best = -1;
   int bestL = nsmax;
   for (int L = nsmax; L >= 8; L = L * 3 / 4) {
     long long tiles = 0, planes = 0;
-    for (const RouteGrid& g : grids) {
+    for (std::size_t i = 0; i < grids.size(); ++i) {
+      const RouteGrid& g = grids[i];
       const int Lg = std::min(L, g.ns), nz = (g.ns + Lg - 1) / Lg;
-      tiles += march_cols(g) * nz;
+      tiles += cols[i] * nz;
       planes = std::max<long long>(planes, (g.ns + nz - 1) / nz + g.r + g.q + 1);
     }
     const long long cost = (tiles + cus - 1) / cus * planes;
