@@ -58,7 +58,6 @@ constexpr int kMaxRec = 65536;
 // parts); with plain addressing the handles are grouped by interior order
 constexpr int kMaxBatch = 64;
 constexpr int kBatchTabSteps = 64;
-constexpr int kMaxItems = 65536;
 constexpr int kMaxGroups = 7;  // seven orders
 
 constexpr int kMaxPart = 1024;
@@ -1255,6 +1254,7 @@ int do_steps_group(sbp_ctx** hs, int n, int nsteps, const double* dt, bool tile)
 // whether a grid of a batch runs in a tile-kernel group: as use_tile, but a
 // shape that sbp_autotune chose for the grid alone does not count
 bool batch_tile(const sbp_ctx* h) { return !h->shape_set && !h->plain && h->g.n <= kTileNodes; }
+
 // The grids of a batch that run in tile-kernel groups (small, by rising size)
 // and those that run over the work list (large).  Small grids stay on the list
 // unless they are at least half of the batch's nodes: a few beside large ones

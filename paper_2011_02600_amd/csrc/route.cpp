@@ -138,16 +138,17 @@ double list_us(const std::vector<RouteGrid>& grids) {
     int planes;
   };
   std::vector<Run> runs;
-  long long total = 0;
+  long long total = 0, items = 0;
   for (const RouteGrid& g : by) {
     order = std::max(order, g.order);
     const int Lg = std::min(L, g.ns), nz = (g.ns + Lg - 1) / Lg;
     const int edge = (g.nr + 63) / 64 + (edge_row(g.nr, 8) ? (g.nq - 1 + 63) / 64 : 0);
     runs.push_back({march_cols(g) * nz, (g.ns + nz - 1) / nz + g.r + g.q + 1});
     runs.push_back({(long long)edge * ((g.ns + 7) / 8), 4});
+    items += (march_cols(g) + edge) * ((g.ns + 7) / 8);
     for (std::size_t i = runs.size() - 2; i < runs.size(); ++i) total += runs[i].n * runs[i].planes;
   }
-  if (grids[0].es == 8 && order >= 7) return 1e30;
+  if (items > kMaxItems || (grids[0].es == 8 && order >= 7)) return 1e30;
   long long last = 0, acc = 0;
   std::size_t at = 0;
   for (int x = 0; x < 8; ++x) {

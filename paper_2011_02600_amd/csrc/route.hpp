@@ -50,7 +50,10 @@ double tile_us(const RouteGrid& g, double cache);
 // that minimises waves of one block per unit times the planes of a block (its
 // chunk plus the warm-up planes).
 int list_chunk(const std::vector<RouteGrid>& grids, int cus);
-// Estimated us per stage of a batch over the work list (no grids: 0).
+// Estimated us per stage of a batch over the work list (no grids: 0; 1e30 if the
+// list could be longer than kMaxItems, with chunks of 8 planes, or does not serve
+// the orders).
+constexpr int kMaxItems = 65536;
 double list_us(const std::vector<RouteGrid>& grids);
 
 // Cuts a batch's tile-kernel grids (the bytes of their fields, in the order in

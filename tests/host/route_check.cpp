@@ -110,6 +110,9 @@ static void lists() {
     }
   }
   check(list_us({}) == 0.0, "empty list");
+  const RouteGrid thin{4, 106000, 4, 2, 0, 2, 4, bytes(4, 106000, 4, 4)};
+  check(list_us({thin, thin, thin, thin}) < 1e30, "a list that fits");
+  check(list_us(std::vector<RouteGrid>(5, thin)) == 1e30, "a list that could be too long");
 }
 
 int main() {
