@@ -117,7 +117,7 @@ struct sbp_ctx {
   bool shape_set = false;    // launch shape ty, zchunk of the caller's (sbp_set_launch)
   bool shape_tuned = false;  // and of sbp_autotune's, where the tile kernel was not the faster or not timed
   TileShape tile{};        // tile kernel's launch shape
-  bool tile_ok = false;    // tile_stage(): whether its stages are the tile kernel's by default
+  bool tile_ok = false, tile_rhs_ok = false;  // tile_stage(), tile_rhs(): the automatic choices
   // launch timing (sbp_set_profiling)
   bool prof = false;
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
@@ -446,19 +446,12 @@ bool use_tile(const sbp_ctx* h) {
   return !h->shape_set && !h->shape_tuned && !h->plain && h->tile_ok;
 }
 
-// The same for a right-hand side alone without penalties (the reverse sweep's).
-// It stores 9 words per node fewer, which the march, bound by its chain, gains
-// nothing from: in single precision the tile kernel stays ahead up to 4.5
-// million nodes (order 6, tile and march with its edge launch: 2.15e6 nodes 119
-// and 136 us, 4.17e6 nodes 43 us less, 7.19e6 13 us more; order 8 equal); in
-// double precision they take turns above kTileNodes.  sbp_autotune's shape does
-// not count where the automatic choice of a stage is the march: it is the
-// fastest of the march's, and the tile kernel was not among what it timed.
-constexpr std::size_t kTileRhsNodes = 4500000;
-
+// The same for a right-hand side alone without penalties (the reverse sweep's;
+// tile_rhs).  sbp_autotune's shape does not count where the automatic choice of
+// a stage is the march: it is the fastest of the march's, and the tile kernel
+// was not among what it timed.
 bool use_tile_rhs(const sbp_ctx* h) {
-  return use_tile(h) || (h->dtype == SBP_F32 && !h->shape_set && !h->plain && !h->tile_ok &&
-                         h->g.n <= kTileRhsNodes);
+  return !h->shape_set && !(h->shape_tuned && h->tile_ok) && !h->plain && h->tile_rhs_ok;
 }
 
 // bytes of a grid's fields: two states, the Runge-Kutta register and the
@@ -1921,6 +1914,7 @@ int sbp_init_grid(sbp_handle* out, int nq, int nr, int ns, const double* xyz, in
     return fail(SBP_EINVAL, "closure construction failed: %s", err);
   }
   h->tile_ok = tile_stage(route_grid(h));
+  h->tile_rhs_ok = tile_rhs(route_grid(h));
   {
     // closure rows: h D+ and h D- at the left end, then their negatives,
     // which are the right-end rows of h D+ and h D- against reversed columns

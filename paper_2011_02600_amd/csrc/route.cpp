@@ -81,6 +81,23 @@ bool tile_stage(const RouteGrid& g) {
   return tile_us(g, 270e6) <= march;
 }
 
+// A right-hand side stores 9 words per node fewer than a stage, which the march,
+// bound by its chain, gains nothing from: in single precision the tile kernel is
+// ahead up to some 4.5 million nodes (order 6: 2.15e6 nodes 119 and 136 us, 4.17e6
+// 43 us less than the march with its edge launch, 7.19e6 13 us more), except
+// where its tiles leave lanes idle at order 8 (whole transposed operator, us:
+// 65 x 65 x 1000 1066 and 948, 257 x 257 x 60 833 and 794, 72 x 72 x 330 479 and
+// 524).  The constants are fitted to 85 grids of 5e5 to 4.5e6 nodes, orders 2 to
+// 8; the rule costs at most 3 % against the better of both (40 x 40 x 2500, order
+// 6).  In double precision both take turns above kTileNodes.
+bool tile_rhs(const RouteGrid& g) {
+  if (g.es == 8) return tile_stage(g);
+  if ((std::size_t)g.nq * g.nr * g.ns > kTileRhsNodes) return false;
+  static const double rate[7] = {20.8, 23.9, 24.6, 24.3, 27.8, 30.6, 38.3};
+  return rate[g.order - 2] * 1e-6 * kTileNT * tile_shape(g.nq, g.nr, g.ns, g.order).ntiles <=
+         15.4 + 2.96 * march_split(march_cols(g), g.ns, g.r + g.q + 1, 256).planes;
+}
+
 double tile_us(const RouteGrid& g, double cache) {
   static const double rate[2][2][7] = {{{36, 36, 42, 45, 48, 55, 80}, {58, 60, 64, 67, 70, 74, 85}},
                                        {{82, 82, 90, 103, 112, 120, 130}, {99, 105, 109, 114, 130, 130, 142}}};

@@ -41,6 +41,9 @@ MarchSplit march_split(long long cols, int ns, int warm, int cus);
 // than as the march with its edge and penalty launches.
 constexpr std::size_t kTileNodes = 1750000;
 bool tile_stage(const RouteGrid& g);
+// The same for a right-hand side alone, without penalties.
+constexpr std::size_t kTileRhsNodes = 4500000;
+bool tile_rhs(const RouteGrid& g);
 
 // Estimated us per stage of the tile kernel on a grid; `cache`: bytes of fields
 // that stay in the memory-side cache.

@@ -78,6 +78,23 @@ static void stages() {
     }
   }
   check(!tile_stage({130, 130, 104, 6, 2, 4, 8, bytes(130, 130, 104, 8)}), "above the limit");
+  // the whole transposed operator, in single precision
+  static const Row rhs[] = {
+      {4, 8, 65, 65, 1000, 1065.8, 947.6}, {4, 8, 65, 65, 400, 468.7, 442.4},  {4, 8, 40, 40, 2500, 1351.6, 1280.9},
+      {4, 8, 257, 257, 60, 833.3, 794.0},  {4, 8, 72, 72, 330, 478.9, 524.4},  {4, 8, 65, 65, 200, 260.9, 272.6},
+      {4, 4, 72, 72, 330, 436.4, 480.2},   {4, 2, 40, 40, 1000, 484.4, 505.6}, {4, 6, 33, 33, 1500, 424.4, 483.8},
+      {4, 4, 20, 20, 4000, 646.3, 737.9},  {4, 2, 257, 257, 60, 709.6, 736.6}, {4, 6, 117, 117, 117, 416.3, 426.8},
+  };
+  for (const Row& x : rhs) {
+    const RouteGrid g{x.nq, x.nr, x.ns, x.order, r[x.order], q[x.order], x.es, bytes(x.nq, x.nr, x.ns, x.es)};
+    if (tile_rhs(g) != (x.tile < x.march)) {
+      std::printf("right-hand side, order %d %d x %d x %d: %s\n", x.order, x.nq, x.nr, x.ns, tile_rhs(g) ? "tile" : "march");
+      ++bad;
+    }
+  }
+  check(tile_rhs({129, 129, 129, 6, 2, 4, 4, bytes(129, 129, 129, 4)}), "129^3");
+  check(!tile_rhs({129, 129, 129, 6, 2, 4, 8, bytes(129, 129, 129, 8)}), "129^3 in double precision");
+  check(!tile_rhs({166, 166, 166, 6, 2, 4, 4, bytes(166, 166, 166, 4)}), "above the right-hand sides' limit");
 }
 
 // measured us per stage of k grids in groups of the tile kernel and on the work

@@ -161,3 +161,21 @@ def test_single_precision_reverse_sweep_on_the_march(order, shape, variant):
     for got, ref, tol in ((rhs["march"], want, 1e-5), (grads["march"], grads["double"], 1e-4)):
         for g, w in zip(got, ref):
             assert np.abs(g - w).max() <= tol * np.abs(w).max()
+
+
+def test_right_hand_sides_the_march_serves_better():
+    """Order 8 in single precision on 65 x 65 columns: the reverse sweep's
+    right-hand sides are the march's, bit for bit those of a caller's shape; on 64
+    x 64 columns the tile kernel's."""
+    from paper_2011_02600_amd import sbp
+    for shape, march in (((400, 65, 65), True), ((400, 64, 64), False)):
+        ns, nr, nq = shape
+        s = sbp.Solver(W.unit_cube(nq, nr, ns), order=8, dtype="f32", gamma=GAMMA)
+        s.set_material(*W.random_medium(shape, 4))
+        lam = torch.from_numpy(W.random_state(shape, 6, smooth=True)).cuda()
+        auto = s.adjoint_rhs(lam).clone()
+        s.set_launch(8, 0)
+        shaped = s.adjoint_rhs(lam)
+        assert torch.equal(auto, shaped) == march
+        assert float((auto - shaped).abs().max()) <= 1e-5 * float(shaped.abs().max())
+        s.close()
