@@ -1248,7 +1248,8 @@ int do_steps_group(sbp_ctx** hs, int n, int nsteps, const double* dt, bool tile)
 // shape that sbp_autotune chose for the grid alone does not count
 bool batch_tile(const sbp_ctx* h) { return !h->shape_set && !h->plain && h->g.n <= kTileNodes; }
 
-// The grids of a batch that run in tile-kernel groups (small, by rising size)
+// The grids of a batch that run in tile-kernel groups (small, by order, whose
+// grids share their launches, and rising size)
 // and those that run over the work list (large).  Small grids stay on the list
 // unless they are at least half of the batch's nodes: a few beside large ones
 // fill the list's gaps (32 cubes of 65 to 193 points, 8 % of the nodes in small
@@ -1272,10 +1273,10 @@ void batch_split(sbp_ctx* const* hs, int n, std::vector<int>& small, std::vector
       large.push_back(g);
       with.push_back(r);
       without.push_back(r);
-    } else if (r.bytes > kGroupBytes || !hs[g]->tile_ok) {
+    } else if (r.bytes > kOwnBytes || !hs[g]->tile_ok) {
       open.push_back(g);
       with.push_back(r);
-      tile += tile_us(r, kGroupBytes);
+      tile += tile_us(r);
     } else {
       small.push_back(g);
     }
@@ -1285,7 +1286,9 @@ void batch_split(sbp_ctx* const* hs, int n, std::vector<int>& small, std::vector
     to.insert(to.end(), open.begin(), open.end());
     std::sort(large.begin(), large.end());
   }
-  std::stable_sort(small.begin(), small.end(), [&](int a, int b) { return hs[a]->g.n < hs[b]->g.n; });
+  std::stable_sort(small.begin(), small.end(), [&](int a, int b) {
+    return hs[a]->order != hs[b]->order ? hs[a]->order < hs[b]->order : hs[a]->g.n < hs[b]->g.n;
+  });
 }
 
 // A batch's grids are independent, so it runs in groups, each all its steps
@@ -1321,7 +1324,10 @@ int do_steps_batch(sbp_ctx** hs, int n, int nsteps, const double* dt) {
   for (int g : large) add(g);
   int rc = run(false);
   std::vector<double> bytes;
-  for (int g : small) bytes.push_back(field_bytes(hs[g]));
+  for (int g : small) {
+    const std::size_t* f = hs[g]->face_n;
+    bytes.push_back(field_bytes(hs[g]) + 2.0 * kNumFaceCoef * (f[0] + f[2] + f[4]) * hs[g]->esize);
+  }
   int i = 0;
   for (int end : tile_groups(bytes)) {
     if (rc) break;

@@ -58,6 +58,8 @@ static long long march_cols(const RouteGrid& g) {
          (long long)(tile_bounds(g.nr - edge_row(g.nr, 8), 8, g.order).size() - 1);
 }
 
+static double tile_us(const RouteGrid& g, double cache);
+
 // The tile kernel reads the planes around a node again for every node, which
 // costs little while the caches hold them; the march reads them once, in a chain
 // of planes whose latency small grids cannot hide.  Near-cubic grids meet
@@ -98,12 +100,14 @@ bool tile_rhs(const RouteGrid& g) {
          15.4 + 2.96 * march_split(march_cols(g), g.ns, g.r + g.q + 1, 256).planes;
 }
 
-double tile_us(const RouteGrid& g, double cache) {
+static double tile_us(const RouteGrid& g, double cache) {
   static const double rate[2][2][7] = {{{36, 36, 42, 45, 48, 55, 80}, {58, 60, 64, 67, 70, 74, 85}},
                                        {{82, 82, 90, 103, 112, 120, 130}, {99, 105, 109, 114, 130, 130, 142}}};
   return rate[g.es == 8][g.bytes > cache][g.order - 2] * 1e-6 * kTileNT *
          tile_shape(g.nq, g.nr, g.ns, g.order).ntiles;
 }
+
+double tile_us(const RouteGrid& g) { return tile_us(g, kOwnBytes); }
 
 int list_chunk(const std::vector<RouteGrid>& grids, int cus) {
   int nsmax = 0;
@@ -189,16 +193,17 @@ double list_us(const std::vector<RouteGrid>& grids) {
   return grids[0].es == 8 ? 150.0 + 8.0 * last : (order == 8 ? 150.0 + 6.6 * last : 60.0 + 5.1 * last);
 }
 
-// us per stage of 16 shots of 64^3, order 4 (41.5 MB each in single precision),
+// us per stage of 16 shots of 64^3, order 4 (43 MB each in single precision),
 // with the work list and in groups of 1, 2, 3, 4, 6, 8 and 16: single
 // precision 289, and 355, 286, 258, 233, 258, 294, 288; double 562, and 570,
-// 476, 469, 538, 532, 520, 507.  The bytes are those of the padded rows: counted
-// by nodes, groups of grids whose rows fill their lines badly leave the cache
-// (47 of 40^3, order 4: 337 us, 278 in groups of the right size, 327 with the
-// work list; 31 of 34 x 101 x 29, order 6: 516, 415 and 431).  Over 112 batches
-// of random shapes 240 MB is best: 200 and 225 MB halve groups of two grids of
-// 104 and 120 MB (480 to 576 us, 233 to 256), 250 MB costs up to 14 % on small
-// grids.
+// 476, 469, 538, 532, 520, 507.  The bytes are those of the padded rows and the
+// face coefficients: counted by nodes, groups of grids whose rows fill their lines
+// badly leave the cache (47 of 40^3, order 4: 337 us, 278 in groups of the right
+// size, 327 with the work list; 31 of 34 x 101 x 29, order 6: 516, 415 and 431).
+// 250 MB in groups of like size, by order: over 112 batches of one shape 2.6 % and
+// over 53 uneven ones 3.7 % less time than 1.28 million nodes a group by size,
+// none slower by more than 2 %; 240 MB of fields by size were 13 % slower on a
+// batch that just exceeds them.
 std::vector<int> tile_groups(const std::vector<double>& bytes) {
   double left = 0.0, sum = 0.0;
   int groups = bytes.empty() ? 0 : 1;

@@ -45,9 +45,10 @@ bool tile_stage(const RouteGrid& g);
 constexpr std::size_t kTileRhsNodes = 4500000;
 bool tile_rhs(const RouteGrid& g);
 
-// Estimated us per stage of the tile kernel on a grid; `cache`: bytes of fields
-// that stay in the memory-side cache.
-double tile_us(const RouteGrid& g, double cache);
+// Estimated us per stage of the tile kernel on one grid of a batch.  Fields above
+// kOwnBytes do not stay in the memory-side cache from stage to stage.
+constexpr double kOwnBytes = 240e6;
+double tile_us(const RouteGrid& g);
 
 // Planes per s-chunk of a batch's work list over `cus` compute units: the length
 // that minimises waves of one block per unit times the planes of a block (its
@@ -59,13 +60,13 @@ int list_chunk(const std::vector<RouteGrid>& grids, int cus);
 constexpr int kMaxItems = 65536;
 double list_us(const std::vector<RouteGrid>& grids);
 
-// Cuts a batch's tile-kernel grids (the bytes of their fields, in the order in
-// which they run) into groups; returns the end of each.  A group's grids run
-// all their steps before the next group's, in launches they share, so its
-// fields should stay in the 256 MB memory-side cache from stage to stage: at
-// most kGroupBytes, and as few groups as that takes, of like size (one grid
-// left over fills the chip worst).
-constexpr double kGroupBytes = 240e6;
+// Cuts a batch's tile-kernel grids (the bytes of their fields and faces, in the
+// order in which they run) into groups; returns the end of each.  A group's grids
+// run all their steps before the next group's, in launches they share per order,
+// so what they read should stay in the 256 MB memory-side cache from stage to
+// stage: at most kGroupBytes, and as few groups as that takes, of like size (one
+// grid left over fills the chip worst).
+constexpr double kGroupBytes = 250e6;
 std::vector<int> tile_groups(const std::vector<double>& bytes);
 
 }  // namespace sbp

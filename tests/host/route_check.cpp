@@ -23,16 +23,19 @@ static double bytes(int nq, int nr, int ns, int es) {
   return 39.0 * es * ((double)((nq - 1 + line - 1) / line * line) + 1) * nr * ns;
 }
 
+// and of its face coefficients, 10 per face node
+static double cube(int n, int es) { return bytes(n, n, n, es) + 60.0 * es * n * n; }
+
 static void groups() {
   check(tile_groups({}).empty(), "no grids");
   check(tile_groups({1e9}) == std::vector<int>{1}, "one grid over the limit");
   check(tile_groups({1e9, 1e9, 1e9}) == std::vector<int>({1, 2, 3}), "grids over the limit");
-  // 16 and 9 shots of 64^3: groups of like size
-  check(tile_groups(std::vector<double>(16, bytes(64, 64, 64, 4))) == std::vector<int>({4, 8, 12, 16}), "16 of 64^3");
-  check(tile_groups(std::vector<double>(9, bytes(64, 64, 64, 4))).size() == 2, "9 of 64^3");
-  check(tile_groups(std::vector<double>(9, bytes(64, 64, 64, 8))).back() == 9, "9 of 64^3 in double precision");
+  // 16 and 9 shots of 64^3 (41.5 MB of fields): groups of like size
+  check(tile_groups(std::vector<double>(16, cube(64, 4))) == std::vector<int>({4, 8, 12, 16}), "16 of 64^3");
+  check(tile_groups(std::vector<double>(9, cube(64, 4))).size() == 2, "9 of 64^3");
+  check(tile_groups(std::vector<double>(9, cube(64, 8))).back() == 9, "9 of 64^3 in double precision");
   // padded rows: 40^3 fills 64 of its rows' places
-  const std::vector<double> b(47, bytes(40, 40, 40, 4));
+  const std::vector<double> b(47, cube(40, 4));
   for (std::size_t n = 1, i = 0; n <= 64; ++n) {
     // rising sizes
     std::vector<double> v;
@@ -120,9 +123,9 @@ static void lists() {
   static const int r[9] = {0, 0, 0, 1, 1, 2, 2, 3, 3}, q[9] = {0, 0, 2, 2, 3, 3, 4, 4, 5};
   for (const Row& x : rows) {
     const RouteGrid g{x.nq, x.nr, x.ns, x.order, r[x.order], q[x.order], x.es, bytes(x.nq, x.nr, x.ns, x.es)};
-    if ((x.k * tile_us(g, kGroupBytes) <= list_us(std::vector<RouteGrid>(x.k, g))) != (x.tile < x.list)) {
+    if ((x.k * tile_us(g) <= list_us(std::vector<RouteGrid>(x.k, g))) != (x.tile < x.list)) {
       std::printf("%d of %d x %d x %d, order %d (%d bytes): tile %.0f list %.0f\n", x.k, x.nq, x.nr, x.ns, x.order, x.es,
-                  x.k * tile_us(g, kGroupBytes), list_us(std::vector<RouteGrid>(x.k, g)));
+                  x.k * tile_us(g), list_us(std::vector<RouteGrid>(x.k, g)));
       ++bad;
     }
   }

@@ -2,7 +2,7 @@
 the caller's keeps a small grid off the tile kernel, so that the work list and
 the launches per order run on grids the oracle can follow; batches of small
 and larger grids split by the rule on their nodes (small: up to 1.75 million;
-apart if they hold at least half), in groups of at most 240 MB of fields."""
+apart if they hold at least half), in groups of at most 250 MB."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,7 @@ from oracle import elastic as E
 pytestmark = pytest.mark.gpu
 
 TOL = {"f64": 1e-12, "f32": 2e-5}  # as in test_gpu_boundary.py
-SMALL, GROUP_BYTES = 1750000, 240e6
+SMALL, GROUP_BYTES = 1750000, 250e6
 
 
 def rel_l2(got, want):
