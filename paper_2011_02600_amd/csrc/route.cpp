@@ -58,56 +58,82 @@ static long long march_cols(const RouteGrid& g) {
          (long long)(tile_bounds(g.nr - edge_row(g.nr, 8), 8, g.order).size() - 1);
 }
 
-static double tile_us(const RouteGrid& g, double cache);
+// What the estimates below depend on: millions of lanes of the tile kernel's
+// tiles, used or not; millions of elements of a field with its padded rows;
+// whether rows of 64, 128 or 256 elements keep whole fields on few memory
+// channels, and whether the tiles then also start inside a line (a last tile of
+// 16 + r columns for r < m left over; not where one column more joins it).
+struct RouteSize {
+  double lanes, padded;
+  bool even, split;
+  long long planes;  // of the march, per compute unit
+};
+static RouteSize route_size(const RouteGrid& g) {
+  RouteSize z;
+  const TileShape t = tile_shape(g.nq, g.nr, g.ns, g.order);
+  const int line = 128 / g.es, pitch = (g.nq - 1 + line - 1) / line * line;
+  z.lanes = 1e-6 * kTileNT * t.ntiles;
+  z.padded = 1e-6 * (pitch + 1.0) * g.nr * g.ns;
+  z.even = (pitch == 64 || pitch == 128 || pitch == 256) && t.q.last != kTileW;
+  z.split = z.even && t.q.T > 1 && g.nq % 32 && g.nq % 32 < g.order;
+  z.planes = march_split(march_cols(g), g.ns, g.r + g.q + 1, 256).planes;
+  return z;
+}
 
 // The tile kernel reads the planes around a node again for every node, which
 // costs little while the caches hold them; the march reads them once, in a chain
 // of planes whose latency small grids cannot hide.  Near-cubic grids meet
 // between 1.6 and 2.1 million nodes (us per stage, tile and march: order 6
 // single 1.44e6 nodes 96 and 120, 2.15e6 141 and 136; double 1.44e6 214 and 231,
-// 2.15e6 311 and 298).  Below that the shape decides in single precision: the
-// tile kernel's time goes with the lanes of its tiles, used or not, at a rate
-// that depends on whether the fields fit the memory-side cache, the march's
-// with the planes of a compute unit.  The constants (us per million lanes, us
-// per plane) are fitted to 160 grids of 2e4 to 1.75e6 nodes, orders 2 to 8; the
-// rule then is nowhere more than 1 % slower than the march (by nodes alone:
-// order 8 at 65 x 65 x 400 181 and 127 us, at 117^3 153 and 142; order 4 at 40 x
-// 40 x 1000 177 and 149) and keeps all but 9 % of the tile kernel's gains.  In
-// double precision, where the march has two more launches and is bound by its
-// registers, the tile kernel is ahead on 85 of 87 grids, at most 3 % behind
-// (order 6 at 65 x 65 x 400: 262 and 253 us).
+// 2.15e6 311 and 298).  Below that the shape decides in single precision.  The
+// tile kernel's time goes with its lanes while the fields fit the memory-side
+// cache, else with their padded bytes, more of them on rows of 64 and 128
+// elements; the march's with the planes of a compute unit, the bytes and the
+// faces.  The constants (us) are fitted to 306 grids of 2e4 to 1.75e6 nodes, orders
+// 2 to 8, where the rule is more than 1 % slower than the march on one (6 %, order
+// 8 at 1001 x 40 x 40) and gives away at most 7 % of the tile kernel's gains; by
+// nodes alone the tile kernel was slower on 60, by up to 43 % (order 8 at 65 x 65 x
+// 400 181 and 127 us, order 5 at 100 x 120 x 130 170 and 133, order 3 at 34 x 167 x
+// 171 139 and 113).  In double precision, where the march has two more launches
+// and is bound by its registers, the tile kernel is ahead on 200 of 203 grids and
+// at most 3 % behind (order 6 at 65 x 65 x 400: 262 and 253 us).
 bool tile_stage(const RouteGrid& g) {
   if ((std::size_t)g.nq * g.nr * g.ns > kTileNodes) return false;
   if (g.es == 8) return true;
-  const double march = 20.0 + (5.6 - 0.1 * g.order) * march_split(march_cols(g), g.ns, g.r + g.q + 1, 256).planes;
-  return tile_us(g, 270e6) <= march;
+  const RouteSize z = route_size(g);
+  const int o = g.order, o8 = o == 8;
+  const double out = std::min(1.0, std::max(0.0, (g.bytes - 255e6) / 30e6));  // share beyond the cache
+  const double tile = 11.0 + (1.0 - out) * (15.9 + 4.2 * o + 17.6 * o8) * z.lanes +
+                      out * (42.0 + 3.3 * o + 10.7 * o8 + 6.6 * z.even + 13.9 * z.split) * z.padded;
+  const double march = 18.6 + (3.3 + 0.07 * o) * z.planes + 13.8 * z.padded + 7.8e-5 * g.nq * (g.nr + g.ns);
+  return tile <= march;
 }
 
 // A right-hand side stores 9 words per node fewer than a stage, which the march,
 // bound by its chain, gains nothing from: in single precision the tile kernel is
 // ahead up to some 4.5 million nodes (order 6: 2.15e6 nodes 119 and 136 us, 4.17e6
-// 43 us less than the march with its edge launch, 7.19e6 13 us more), except
-// where its tiles leave lanes idle at order 8 (whole transposed operator, us:
-// 65 x 65 x 1000 1066 and 948, 257 x 257 x 60 833 and 794, 72 x 72 x 330 479 and
-// 524).  The constants are fitted to 85 grids of 5e5 to 4.5e6 nodes, orders 2 to
-// 8; the rule costs at most 3 % against the better of both (40 x 40 x 2500, order
-// 6).  In double precision both take turns above kTileNodes.
+// 43 us less than the march with its edge launch, 7.19e6 13 us more), except on
+// many shapes at order 8, whose tiles leave lanes idle, and on rows of 64 and 128
+// elements (whole transposed operator, us: order 8 at 65 x 65 x 1000 1066 and 948,
+// at 257 x 257 x 60 833 and 794, at 72 x 72 x 330 479 and 524; order 6 at 100 x 190 x
+// 139 703 and 674).  The constants are fitted to 198 grids of up to 4.5e6 nodes,
+// orders 2 to 8; the rule costs at most 3 % against the better of both.  In double
+// precision both take turns above kTileNodes.
 bool tile_rhs(const RouteGrid& g) {
   if (g.es == 8) return tile_stage(g);
   if ((std::size_t)g.nq * g.nr * g.ns > kTileRhsNodes) return false;
-  static const double rate[7] = {20.8, 23.9, 24.6, 24.3, 27.8, 30.6, 38.3};
-  return rate[g.order - 2] * 1e-6 * kTileNT * tile_shape(g.nq, g.nr, g.ns, g.order).ntiles <=
-         15.4 + 2.96 * march_split(march_cols(g), g.ns, g.r + g.q + 1, 256).planes;
+  const RouteSize z = route_size(g);
+  const int o8 = g.order == 8;
+  return (1.5 + 1.6 * g.order - 12.0 * o8 + 4.1 * z.even + 8.4 * z.split) * z.padded + (14.7 + 14.0 * o8) * z.lanes <=
+         13.3 + 3.0 * z.planes - 1.1e-4 * g.nr * g.ns;
 }
 
-static double tile_us(const RouteGrid& g, double cache) {
+double tile_us(const RouteGrid& g) {
   static const double rate[2][2][7] = {{{36, 36, 42, 45, 48, 55, 80}, {58, 60, 64, 67, 70, 74, 85}},
                                        {{82, 82, 90, 103, 112, 120, 130}, {99, 105, 109, 114, 130, 130, 142}}};
-  return rate[g.es == 8][g.bytes > cache][g.order - 2] * 1e-6 * kTileNT *
+  return rate[g.es == 8][g.bytes > kOwnBytes][g.order - 2] * 1e-6 * kTileNT *
          tile_shape(g.nq, g.nr, g.ns, g.order).ntiles;
 }
-
-double tile_us(const RouteGrid& g) { return tile_us(g, kOwnBytes); }
 
 int list_chunk(const std::vector<RouteGrid>& grids, int cus) {
   int nsmax = 0;

@@ -68,6 +68,9 @@ static void stages() {
       {4, 4, 65, 65, 400, 71.9, 105.6},    {4, 4, 40, 40, 1000, 177.0, 148.8},  {4, 4, 20, 20, 4000, 197.5, 264.5},
       {4, 6, 65, 65, 49, 18.0, 82.0},      {4, 6, 257, 257, 26, 102.8, 119.4},  {4, 6, 40, 40, 1000, 190.0, 161.3},
       {4, 6, 1001, 40, 40, 94.8, 124.9},   {4, 7, 40, 40, 1000, 201.6, 167.7},  {4, 7, 513, 200, 16, 103.0, 143.2},
+      {4, 3, 34, 167, 171, 138.8, 112.9},  {4, 5, 34, 180, 180, 173.9, 132.6},  {4, 3, 33, 180, 180, 44.0, 99.8},
+      {4, 5, 100, 120, 130, 169.9, 133.3}, {4, 5, 66, 120, 130, 67.2, 127.0},   {4, 6, 130, 130, 100, 138.6, 153.1},
+      {4, 3, 40, 160, 160, 74.0, 105.9},   {4, 7, 68, 140, 160, 155.5, 172.2},  {4, 3, 45, 150, 150, 61.5, 95.6},
       {4, 8, 65, 65, 65, 38.2, 93.8},      {4, 8, 97, 97, 97, 95.9, 105.7},     {4, 8, 65, 65, 400, 181.0, 126.9},
       {4, 8, 120, 120, 120, 158.5, 146.0}, {4, 8, 20, 260, 260, 187.5, 249.3},  {4, 8, 40, 40, 1000, 230.9, 184.0},
       {8, 3, 117, 117, 117, 186.2, 231.9}, {8, 6, 120, 120, 120, 247.5, 277.2}, {8, 8, 65, 65, 400, 350.4, 479.0},
@@ -86,6 +89,7 @@ static void stages() {
       {4, 8, 65, 65, 1000, 1065.8, 947.6}, {4, 8, 65, 65, 400, 468.7, 442.4},  {4, 8, 40, 40, 2500, 1351.6, 1280.9},
       {4, 8, 257, 257, 60, 833.3, 794.0},  {4, 8, 72, 72, 330, 478.9, 524.4},  {4, 8, 65, 65, 200, 260.9, 272.6},
       {4, 4, 72, 72, 330, 436.4, 480.2},   {4, 2, 40, 40, 1000, 484.4, 505.6}, {4, 6, 33, 33, 1500, 424.4, 483.8},
+      {4, 6, 100, 190, 139, 702.7, 674.1}, {4, 8, 103, 153, 209, 930.5, 850.5}, {4, 6, 34, 285, 239, 916.0, 880.8},
       {4, 4, 20, 20, 4000, 646.3, 737.9},  {4, 2, 257, 257, 60, 709.6, 736.6}, {4, 6, 117, 117, 117, 416.3, 426.8},
   };
   for (const Row& x : rhs) {
